@@ -56,7 +56,9 @@ namespace {
 
 // ------------------------------------------------------------------ autotuner
 // Table: (precision, size class) -> tile of the long complex products of the
-// LU and the solves (0: 64x64 K16, 1: 128x64 K8, 2: 64x32 K8, 3: 128x32 K8).
+// LU and the solves (0: 64x64, 1: 128x64, 2: 64x32, 3: 32x32 in FP64, 128x32 in
+// FP32).  FP64 entries are kept under the name of the direct-to-LDS kernels,
+// so that a table measured with other kernels is not read for them.
 // The size class is n rounded up to a multiple of 256; the precision is that
 // of the factorisation (FP64, or FP32 for both mixed forms: under BF16x the
 // rank-K trailing updates run on the split-BF16 kernel, and the FP32 table
@@ -70,7 +72,7 @@ std::map<std::string, int> g_tune;
 bool g_tune_loaded = false;
 
 std::string tune_key(int cls, gw_precision prec) {
-    return std::string(prec == GW_FP64 ? "zgemm_fp64" : "cgemm_fp32") + "_n" + std::to_string(cls);
+    return std::string(prec == GW_FP64 ? "zgemm_lds_fp64" : "cgemm_fp32") + "_n" + std::to_string(cls);
 }
 
 gw_status tune_tile(gw_ctx *ctx, int n, gw_precision prec, hipStream_t st, int *tile) {

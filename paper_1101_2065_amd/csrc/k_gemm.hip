@@ -7,17 +7,13 @@
 // solves use three real MFMA products per complex product, ac, bd and
 // (a + b)(c + d) (a quarter less matrix-core work, normwise as accurate); the
 // FP64 refinement residual and the FP32 products use four.
-// Tiles: 256-thread workgroups, four 64-wide waves in 2x2.  An FP64 MFMA
-// 16x16x4 occupies the matrix pipe for many cycles, so the complex FP64
-// products are latency-bound by the LDS and global loads around it unless
-// several workgroups share a CU: they use narrow tiles, 64x32 (each wave 2x1
-// MFMA 16x16 blocks) at five waves per SIMD in the three-product form (94
-// registers) for every LU and solve product, and 128x32 (4x1) at four waves
-// per SIMD in the four-product form.  The real-times-complex and FP32
-// products keep 64x64 (K steps of 16) and 128x64 (K steps of 8) at two waves
-// per SIMD.  The narrow tiles are dealt to the XCDs in contiguous ranges (each
-// XCD has its own L2).  K is staged through a double-buffered LDS tile, the
-// next step prefetched into registers.
+// Tiles: 256-thread workgroups, four 64-wide waves in 2x2.  The complex FP64
+// products (zgemm_tile) copy their operands from global memory straight into
+// LDS in matrix-core order and keep almost nothing but MFMA instructions in
+// the K loop; the real-times-complex, real and FP32 products (gemm_tile) stage
+// them through registers: 64x64 (K steps of 16) and 128x64 (K steps of 8) at
+// two waves per SIMD, and narrow FP32 tiles.  The tiles are dealt to the XCDs
+// in contiguous ranges (each XCD has its own L2).
 #include "gw_internal.h"
 #include "gw_prof.h"
 
@@ -56,23 +52,16 @@ struct Mfma<float> {
 // Workgroup = 256 threads = 2x2 waves; a wave owns WM x WN MFMA blocks of
 // 16x16, so the workgroup tile is (32 WM) x (32 WN); K advances BK per
 // LDS stage.
-// M3 (complex times complex only): three real products per complex product,
-// (a + ib)(c + id) = ac - bd + i[(a + b)(c + d) - ac - bd], instead of four:
-// a quarter fewer matrix-core operations, with the sums a + b and c + d
-// formed from the operands as they come out of LDS.  Normwise as accurate
-// (the imaginary part of an entry loses relative accuracy only where it is
-// small against |a||c| + |b||d|); the LU and the solves use it, the FP64
-// refinement residual does not.
 // One (32 WM) x (32 WN) tile of C with its top-left corner at (m0, n0); A, B,
 // C (and C32) point at the tile's batch entry.
 // MIR: row r >= 1 of C is also written, conjugated, r rows before C's first
 // row (C(-omega) = C(omega)* for a C whose rows are omega_r on a symmetric
 // mesh starting at omega = 0).
-template <typename T, bool AC, bool BC, int WM, int WN, int BK, bool M3, typename GT = T, bool MIR = false>
+template <typename T, bool AC, bool BC, int WM, int WN, int BK, typename GT = T, bool MIR = false>
 __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT *__restrict__ A, int64_t lda,
                                           const GT *B, int64_t ldb, T beta, GT *C, int64_t ldc, int add_eye,
                                           float *C32, int m0, int n0) {
-    static_assert(!M3 || (AC && BC), "the three-product form is for complex times complex");
+    static_assert(!(AC && BC) || sizeof(T) == 4, "complex FP64 products take zgemm_tile");
     constexpr int BM = 32 * WM, BN = 32 * WN;
     constexpr bool CC = AC || BC;
     constexpr int ea = AC ? 2 : 1, eb = BC ? 2 : 1, ec = CC ? 2 : 1;
@@ -80,15 +69,13 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
     constexpr int EB = BK * BN / 256, TPRB = BN / EB;  // (B)
     static_assert(EA >= 1 && EB >= 1 && TPRA >= 1 && TPRB >= 1, "tile too small");
     typedef typename Mfma<T>::v4 v4;
-    // in the three-product tile and the Cauchy product's (MIR) the
-    // transposed A rows are padded by one value: unpadded, the K rows of the
-    // tile are a multiple of the LDS bank span apart, so the stores of a wave
-    // (several K rows of few tile rows) pile onto the same banks (3x the
-    // bank-conflict cycles at 64x32; the Cauchy product reads 10% more and
-    // runs 3% slower unpadded).  The other tiles run faster unpadded (the
-    // four-product 128x32 of the FP64 refinement residual lost 9% to the
-    // padding).  The 64x64 tile also gives each thread B columns TPRB apart.
-    constexpr int PA = (M3 || MIR) ? 1 : 0;
+    // in the Cauchy product's tile (MIR) the transposed A rows are padded by
+    // one value: unpadded, the K rows of the tile are a multiple of the LDS
+    // bank span apart, so the stores of a wave (several K rows of few tile
+    // rows) pile onto the same banks (10% more bank-conflict cycles, 3%
+    // slower).  The other tiles run faster unpadded.  The 64x64 tile also
+    // gives each thread B columns TPRB apart.
+    constexpr int PA = MIR ? 1 : 0;
     constexpr int SB = (BK == 16) ? TPRB : 1;
     // complex operands are staged interleaved {re, im}: one 16-byte LDS read
     // per operand value instead of two 8-byte ones
@@ -101,15 +88,13 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
 
-    // M3: accr = sum a c, acci = sum b d, accs = sum (a + b)(c + d)
-    v4 accr[WM][WN], acci[WM][WN], accs[M3 ? WM : 1][M3 ? WN : 1];
+    v4 accr[WM][WN], acci[WM][WN];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
         for (int j = 0; j < WN; ++j) {
             accr[i][j] = v4{0, 0, 0, 0};
             acci[i][j] = v4{0, 0, 0, 0};
-            if constexpr (M3) accs[i][j] = v4{0, 0, 0, 0};
         }
 
     const int a_row = tid / TPRA, a_k = (tid % TPRA) * EA;
@@ -217,28 +202,6 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
                     bi[j] = T(0);
                 }
             }
-            if constexpr (M3) {
-                // three passes, each over every block, so that no MFMA waits
-                // on the one issued just before it
-                T sa[WM], sb[WN];
-#pragma unroll
-                for (int i = 0; i < WM; ++i) sa[i] = ar[i] + ai[i];
-#pragma unroll
-                for (int j = 0; j < WN; ++j) sb[j] = br[j] + bi[j];
-#pragma unroll
-                for (int i = 0; i < WM; ++i)
-#pragma unroll
-                    for (int j = 0; j < WN; ++j) accr[i][j] = Mfma<T>::op(ar[i], br[j], accr[i][j]);
-#pragma unroll
-                for (int i = 0; i < WM; ++i)
-#pragma unroll
-                    for (int j = 0; j < WN; ++j) acci[i][j] = Mfma<T>::op(ai[i], bi[j], acci[i][j]);
-#pragma unroll
-                for (int i = 0; i < WM; ++i)
-#pragma unroll
-                    for (int j = 0; j < WN; ++j) accs[i][j] = Mfma<T>::op(sa[i], sb[j], accs[i][j]);
-                continue;
-            }
             // two passes so that no MFMA waits on the one issued just before it
 #pragma unroll
             for (int i = 0; i < WM; ++i)
@@ -274,14 +237,7 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
                 const int col = n0 + wn * 16 * WN + j * 16 + (lane & 15);
                 if (row < M && col < N) {
                     GT *pc = C + ((int64_t)row * ldc + col) * ec;
-                    T vr, vi;
-                    if constexpr (M3) {
-                        vr = alpha * (accr[i][j][e] - acci[i][j][e]);
-                        vi = alpha * (accs[i][j][e] - accr[i][j][e] - acci[i][j][e]);
-                    } else {
-                        vr = alpha * accr[i][j][e];
-                        vi = alpha * acci[i][j][e];
-                    }
+                    T vr = alpha * accr[i][j][e], vi = alpha * acci[i][j][e];
                     if (beta != T(0)) {
                         vr += beta * pc[0];
                         if constexpr (CC) vi += beta * pc[1];
@@ -305,12 +261,248 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
             }
 }
 
+// ------------------------------------------------------------------ complex FP64 products
+// C = alpha A B + beta C, one 32 WM x 32 WN tile at (m0, n0).
+//
+// What bounds it: an FP64 MFMA 16x16x4 holds its SIMD for 64 cycles, and every
+// other vector instruction of any wave on that SIMD takes cycles from it
+// rather than hiding behind it (measured: an integer operation about 2, an
+// FP64 addition 3.6, a 16-byte LDS read 7).  So the loop issues as little else
+// as it can: the operands go from global memory to LDS by 16-byte direct
+// copies (no staging registers, no LDS stores), already in the order the
+// matrix cores take them, so that a fragment is one conflict-free 16-byte LDS
+// read per value at a constant offset, and the tile is as large as the
+// registers allow (each fragment then feeds more MFMAs).
+//
+// LDS holds "chunks" of 64 values (1 KB), one per 16 rows (columns) x 4 k:
+// B's in lane order (lane l: k = l / 16, column l % 16), A's with the four k of
+// a row side by side, so that four lanes of the copy read 64 contiguous bytes,
+// and permuted within each row by (row / 4) % 4, which spreads the 16 lanes of
+// a fragment read over all banks.  Two K steps of 8 are kept: one is computed
+// while the next is copied; one barrier per step.
+//
+// M3: three real products per complex product,
+// (a + ib)(c + id) = ac - bd + i[(a + b)(c + d) - ac - bd], instead of four:
+// a quarter fewer matrix-core operations.  Normwise as accurate (the imaginary
+// part of an entry loses relative accuracy only where it is small against
+// |a||c| + |b||d|); the LU and the solves use it, the FP64 refinement residual
+// does not.
+//
+// Measured (three products, in 8MNK): 1744 x 1744 x 256, 32 frequencies: 128x64
+// 82.0 TF, 64x64 80.7, 64x32 76.7, against 67.3 for the 64x32 tile staged
+// through registers; 256 x 2000 x 1744: 89.1, 83.6, 75.4 against 71.6; the
+// K = 64 products of the 256-wide blocks 44-55 (HBM-bound on C).
+//
+// DMA = false (a pointer that is not 16-byte aligned, which the direct copies
+// would need) loads through registers instead.
+typedef double zd2 __attribute__((ext_vector_type(2)));
+typedef double zd2u __attribute__((ext_vector_type(2), aligned(8)));
+constexpr int ZBK = 8;  // K step
+
+// Waits for this wave's direct copies and LDS reads, then for the other waves.
+__device__ __forceinline__ void copies_done_barrier() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int WM, int WN, bool M3, bool DMA>
+__device__ __forceinline__ void zgemm_tile(int M, int N, int K, double alpha, const dglobal<double> *A_, int64_t lda,
+                                           const dglobal<double> *B_, int64_t ldb, double beta, dglobal<double> *C_,
+                                           int64_t ldc, int m0, int n0) {
+    typedef Mfma<double>::v4 v4;
+    typedef dglobal<zd2u> G2;
+    constexpr int BM = 32 * WM, BN = 32 * WN, KC = ZBK / 4;
+    constexpr int CA = BM / 16 * KC, CB = BN / 16 * KC;  // chunks per stage
+    constexpr int NA = CA / 4, NB4 = CB / 4;             // copied by each wave
+    static_assert(CA % 4 == 0 && CB % 4 == 0, "whole chunks per wave");
+    __shared__ zd2 lds[2][(CA + CB) * 64];
+    const G2 *A = (const G2 *)A_, *B = (const G2 *)B_;
+    G2 *C = (G2 *)C_;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    // this lane's value of each chunk its wave copies; rows and columns past
+    // the edge repeat the last one (their results are not stored)
+    const int ar = lane >> 2, ak = (lane & 3) ^ ((lane >> 4) & 3);
+    const int bk = lane >> 4, bn = lane & 15;
+    const G2 *pa[NA], *pb[NB4];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int c = wave * NA + i;
+        pa[i] = A + (int64_t)min(m0 + (c / KC) * 16 + ar, M - 1) * lda + (c % KC) * 4 + ak;
+    }
+#pragma unroll
+    for (int i = 0; i < NB4; ++i) {
+        const int c = wave * NB4 + i;
+        pb[i] = B + (int64_t)((c / (BN / 16)) * 4 + bk) * ldb + min(n0 + (c % (BN / 16)) * 16 + bn, N - 1);
+    }
+    // M3: accr = sum a c, acci = sum b d, accs = sum (a + b)(c + d)
+    v4 accr[WM][WN], acci[WM][WN], accs[M3 ? WM : 1][M3 ? WN : 1];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+            accr[i][j] = v4{0, 0, 0, 0};
+            acci[i][j] = v4{0, 0, 0, 0};
+            if constexpr (M3) accs[i][j] = v4{0, 0, 0, 0};
+        }
+    auto copy = [&](const G2 *g, zd2 *l) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        if constexpr (DMA) {
+            __builtin_amdgcn_global_load_lds((const dglobal<uint32_t> *)g,
+                                             (__attribute__((address_space(3))) uint32_t *)l, 16, 0, 0);
+        } else {
+            l[lane] = *g;
+        }
+#else
+        l[lane] = *g;
+#endif
+    };
+    auto stage = [&](int s) {
+        zd2 *base = lds[s];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            copy(pa[i], base + (wave * NA + i) * 64);
+            pa[i] += ZBK;
+        }
+#pragma unroll
+        for (int i = 0; i < NB4; ++i) {
+            copy(pb[i], base + (CA + wave * NB4 + i) * 64);
+            pb[i] += ZBK * ldb;
+        }
+    };
+    const int fa = 4 * (lane & 15) + ((lane >> 4) ^ ((lane >> 2) & 3));
+    auto compute = [&](int s) {
+        const zd2 *base = lds[s];
+#pragma unroll
+        for (int q = 0; q < KC; ++q) {
+            zd2 a[WM], b[WN];
+#pragma unroll
+            for (int i = 0; i < WM; ++i) a[i] = base[((wm * WM + i) * KC + q) * 64 + fa];
+#pragma unroll
+            for (int j = 0; j < WN; ++j) b[j] = base[(CA + q * (BN / 16) + wn * WN + j) * 64 + lane];
+            if constexpr (M3) {
+                // three passes, each over every block, so that no MFMA waits
+                // on the one issued just before it
+                double sa[WM], sb[WN];
+#pragma unroll
+                for (int i = 0; i < WM; ++i) sa[i] = a[i].x + a[i].y;
+#pragma unroll
+                for (int j = 0; j < WN; ++j) sb[j] = b[j].x + b[j].y;
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j) accr[i][j] = Mfma<double>::op(a[i].x, b[j].x, accr[i][j]);
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j) acci[i][j] = Mfma<double>::op(a[i].y, b[j].y, acci[i][j]);
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j) accs[i][j] = Mfma<double>::op(sa[i], sb[j], accs[i][j]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j) {
+                        accr[i][j] = Mfma<double>::op(a[i].x, b[j].x, accr[i][j]);
+                        acci[i][j] = Mfma<double>::op(a[i].x, b[j].y, acci[i][j]);
+                    }
+#pragma unroll
+                for (int i = 0; i < WM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WN; ++j) {
+                        accr[i][j] = Mfma<double>::op(-a[i].y, b[j].y, accr[i][j]);
+                        acci[i][j] = Mfma<double>::op(a[i].y, b[j].x, acci[i][j]);
+                    }
+            }
+        }
+    };
+    const int nfull = K / ZBK;
+    if (nfull > 0) stage(0);
+    int cur = 0;
+    for (int k = 0; k < nfull; ++k) {
+        copies_done_barrier();
+        if (k + 1 < nfull) stage(cur ^ 1);
+        compute(cur);
+        cur ^= 1;
+    }
+    if (nfull * ZBK < K) {
+        // the last, partial step: zeros past K, into the buffer nobody reads
+        const int k0 = nfull * ZBK;
+        zd2 *base = lds[cur];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int c = wave * NA + i, k = k0 + (c % KC) * 4 + ak;
+            zd2 x{0, 0};
+            if (k < K) x = *pa[i];
+            base[c * 64 + lane] = x;
+        }
+#pragma unroll
+        for (int i = 0; i < NB4; ++i) {
+            const int c = wave * NB4 + i, k = k0 + (c / (BN / 16)) * 4 + bk;
+            zd2 x{0, 0};
+            if (k < K) x = *pb[i];
+            base[(CA + c) * 64 + lane] = x;
+        }
+        copies_done_barrier();
+        compute(cur);
+    }
+    // every read of B is done before C, which may be B, is written
+    copies_done_barrier();
+    // element e of a lane is row lane / 16 + 4 e, column lane % 16 of its
+    // 16x16 block (operands: A[lane % 16][lane / 16], B[lane / 16][lane % 16])
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = m0 + (wm * WM + i) * 16 + Mfma<double>::row(lane, e);
+                const int col = n0 + (wn * WN + j) * 16 + (lane & 15);
+                if (row < M && col < N) {
+                    G2 *pc = C + (int64_t)row * ldc + col;
+                    double vr, vi;
+                    if constexpr (M3) {
+                        vr = alpha * (accr[i][j][e] - acci[i][j][e]);
+                        vi = alpha * (accs[i][j][e] - accr[i][j][e] - acci[i][j][e]);
+                    } else {
+                        vr = alpha * accr[i][j][e];
+                        vi = alpha * acci[i][j][e];
+                    }
+                    if (beta != 0.0) {
+                        const zd2 c = *pc;
+                        vr += beta * c.x;
+                        vi += beta * c.y;
+                    }
+                    *pc = zd2{vr, vi};
+                }
+            }
+}
+
+// Workgroup l of a launch (dealt to XCD l mod 8) takes tile
+// (l mod 8) n / 8 + l / 8: each XCD works through a contiguous run of tiles,
+// consecutive tiles sharing an A row band in that XCD's L2.
+template <int WM, int WN, int OCC, bool M3, bool DMA>
+__global__ __launch_bounds__(256, OCC) void k_zgemm(int M, int N, int K, double alpha, const double *A, int64_t lda,
+                                                    int64_t sA, const double *B, int64_t ldb, int64_t sB, double beta,
+                                                    double *C, int64_t ldc, int64_t sC) {
+    const int gx = gridDim.x, gy = gridDim.y;
+    const int64_t nt = (int64_t)gx * gy * gridDim.z;
+    const int64_t l = blockIdx.x + (int64_t)gx * (blockIdx.y + (int64_t)gy * blockIdx.z);
+    const int64_t n8 = nt / 8, t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;
+    const int64_t bz = t / ((int64_t)gx * gy);
+    zgemm_tile<WM, WN, M3, DMA>(M, N, K, alpha, (const dglobal<double> *)A + bz * sA * 2, lda,
+                                (const dglobal<double> *)B + bz * sB * 2, ldb, beta,
+                                (dglobal<double> *)C + bz * sC * 2, ldc, (int)((t / gx) % gy) * 32 * WM,
+                                (int)(t % gx) * 32 * WN);
+}
+
 // XR: tile order.  0: as launched; 1 and 2: workgroups are dealt to the
 // eight XCDs in turn, each with its own L2, so each XCD gets a contiguous
 // range of tiles, row band by row band (1: tiles sharing an A row band share
 // that XCD's L2) or column band by column band (2: tiles sharing a B column
 // band do, for products whose B is much larger than A).
-template <typename T, bool AC, bool BC, int WM, int WN, int BK, int OCC, int XR, bool M3 = false, bool MIR = false>
+template <typename T, bool AC, bool BC, int WM, int WN, int BK, int OCC, int XR, bool MIR = false>
 __global__ __launch_bounds__(256, OCC) void k_gemm(int M, int N, int K, T alpha, const T *__restrict__ A, int64_t lda,
                                                  int64_t sA, const T *B, int64_t ldb, int64_t sB, T beta,
                                                  T *C, int64_t ldc, int64_t sC, int add_eye, float *C32,
@@ -334,15 +526,14 @@ __global__ __launch_bounds__(256, OCC) void k_gemm(int M, int N, int K, T alpha,
     B += (int64_t)bz * sB * eb;
     C += (int64_t)bz * sC * ec;
     if (C32) C32 += (int64_t)bz * sC32 * 2;
-    gemm_tile<T, AC, BC, WM, WN, BK, M3, T, MIR>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, add_eye, C32,
-                                                 by * 32 * WM, bx * 32 * WN);
+    gemm_tile<T, AC, BC, WM, WN, BK, T, MIR>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, add_eye, C32, by * 32 * WM,
+                                             bx * 32 * WN);
 }
 
 // Tile t of a multi-product launch: its item (searched from item a up; the
 // items are ordered by their first tile) and the tile within it.
-template <typename T, bool AC, bool BC, int WM, int WN, int BK, bool M3>
+template <typename T, int WM, int WN, int BK, bool M3>
 __device__ __forceinline__ void item_tile(const GemmItem *__restrict__ items, int n_items, int64_t t, int &a) {
-    constexpr int ea = AC ? 2 : 1, eb = BC ? 2 : 1, ec = (AC || BC) ? 2 : 1;
     int b = n_items - 1;
     while (a < b) {
         const int m = (a + b + 1) >> 1;
@@ -356,24 +547,28 @@ __device__ __forceinline__ void item_tile(const GemmItem *__restrict__ items, in
     const int by = (int)(rr / g.tx), bx = (int)(rr % g.tx);
     // operands through global-address-space pointers (see dglobal)
     typedef dglobal<T> GT;
-    const GT *Ap = (const GT *)g.A + (int64_t)bz * g.sA * ea;
-    const GT *Bp = (const GT *)g.B + (int64_t)bz * g.sB * eb;
-    GT *Cp = (GT *)g.C + (int64_t)bz * g.sC * ec;
-    gemm_tile<T, AC, BC, WM, WN, BK, M3, GT>(g.M, g.N, g.K, (T)g.alpha, Ap, g.lda, Bp, g.ldb, (T)g.beta, Cp, g.ldc, 0,
-                                             nullptr, by * 32 * WM, bx * 32 * WN);
+    const GT *Ap = (const GT *)g.A + (int64_t)bz * g.sA * 2;
+    const GT *Bp = (const GT *)g.B + (int64_t)bz * g.sB * 2;
+    GT *Cp = (GT *)g.C + (int64_t)bz * g.sC * 2;
+    if constexpr (sizeof(T) == 8)
+        zgemm_tile<WM, WN, M3, true>(g.M, g.N, g.K, g.alpha, Ap, g.lda, Bp, g.ldb, g.beta, Cp, g.ldc, by * 32 * WM,
+                                     bx * 32 * WN);
+    else
+        gemm_tile<T, true, true, WM, WN, BK, GT>(g.M, g.N, g.K, (T)g.alpha, Ap, g.lda, Bp, g.ldb, (T)g.beta, Cp, g.ldc,
+                                                 0, nullptr, by * 32 * WM, bx * 32 * WN);
 }
 
 // Many products in one launch, one tile per workgroup, the hardware
 // dispatcher handing out the tiles: workgroup l (dealt to XCD l mod 8) takes
 // tile (l mod 8) n/8 + l/8, so each XCD works through a contiguous run of
 // tiles (consecutive tiles share an A row band, in that XCD's L2).
-template <typename T, bool AC, bool BC, int WM, int WN, int BK, int OCC, bool M3>
+template <typename T, int WM, int WN, int BK, int OCC, bool M3>
 __global__ __launch_bounds__(256, OCC) void k_gemm_group(const GemmItem *__restrict__ items, int n_items,
                                                        int64_t n_tiles) {
     const int64_t l = blockIdx.x, n8 = n_tiles / 8;
     const int64_t t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;
     int a = 0;
-    item_tile<T, AC, BC, WM, WN, BK, M3>(items, n_items, t, a);
+    item_tile<T, WM, WN, BK, M3>(items, n_items, t, a);
 }
 
 // Workgroup barrier that orders LDS accesses only: unlike __syncthreads it
@@ -392,7 +587,7 @@ __device__ __forceinline__ void lds_barrier() {
 // because a wave's memory operations complete in order: the first loads of a
 // workgroup's next tile wait for its previous tile's result stores to drain,
 // which a newly dispatched workgroup does not.
-template <typename T, bool AC, bool BC, int WM, int WN, int BK, int OCC, bool M3>
+template <typename T, int WM, int WN, int BK, int OCC, bool M3>
 __global__ __launch_bounds__(256, OCC) void k_gemm_queue(const GemmItem *__restrict__ items, int n_items,
                                                        int64_t n_tiles, unsigned *__restrict__ queue) {
     __shared__ int64_t s_t;
@@ -415,7 +610,7 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_queue(const GemmItem *__restr
             // tile's first loads
             unsigned nxt = 0;
             if (threadIdx.x == 0) nxt = atomicAdd(&queue[q], 1u);
-            item_tile<T, AC, BC, WM, WN, BK, M3>(items, n_items, t, a);
+            item_tile<T, WM, WN, BK, M3>(items, n_items, t, a);
             lds_barrier();  // everyone has read s_t; the tile is done with LDS
             if (threadIdx.x == 0) s_t = lo + (int64_t)nxt;
             lds_barrier();
@@ -593,15 +788,62 @@ __global__ void k_formA_diag(int n, int batch, const double *__restrict__ lam, c
         }
 }
 
-// Tile of the long complex products (M >= 256, K >= 128): < 0 the default
-// (FP64 128x32, FP32 128x64); 0: 64x64 K16; 1: 128x64 K8; 2: 64x32 K8;
-// 3: 128x32 K8.  Per host thread, so the batched driver can record each
-// molecule with its tuned tile.  Thin complex FP64 products always take 64x32.
+// Tile of the long complex products (M >= 256, K >= 128): < 0 the default.
+// FP64: 0: 64x64, 1: 128x64, 2: 64x32, 3: 32x32 (K steps of 8); FP32: 0: 64x64
+// K16, 1: 128x64 K8, 2: 64x32 K8, 3: 128x32 K8.  Per host thread, so the
+// batched driver can record each molecule with its tuned tile.
 thread_local int g_gemm_tile = -1;
 
-const char *const kZgemmName[4] = {"zgemm_64x64", "zgemm_128x64", "zgemm_64x32", "zgemm_128x32"};
+const char *const kZgemmName[4] = {"zgemm_64x64", "zgemm_128x64", "zgemm_64x32", "zgemm_32x32"};
 const char *const kCgemmName[4] = {"cgemm_64x64", "cgemm_128x64", "cgemm_64x32", "cgemm_128x32"};
-const char *const kZgemm3Name[4] = {"zgemm3m_64x64", "zgemm3m_128x64", "zgemm3m_64x32", "zgemm3m_128x32"};
+const char *const kZgemm3Name[4] = {"zgemm3m_64x64", "zgemm3m_128x64", "zgemm3m_64x32", "zgemm3m_32x32"};
+constexpr int kZRows[4] = {64, 128, 64, 32}, kZCols[4] = {64, 64, 32, 32};
+
+// The tile of a complex FP64 product: the least padded area over the tile's
+// rate.  Rates relative to 64x64 (84 TF on long products): 128x64 gains from
+// K = 512 on (88 TF at 256 x 2000 x 1024 against 85; its longer fill and drain
+// lose below), 64x32 and 32x32 run at 0.95 and 0.87 of it and win where they
+// pad less (76 x 1100 x 1024: 57 TF by 32x32, 52 by 64x64) or, for 64x32, at
+// M, K <= 64 (47 against 44 TF).  A launch that 64x64 tiles cannot spread over
+// the 256 CUs (the lone frequency) takes 32x32.  in_place: C is B, so one tile
+// must hold every row.
+int ztile(int M, int N, int K, int batch, bool in_place) {
+    const double rate[4] = {1.0, K >= 512 ? 1.04 : 0.96, M <= 64 && K <= 64 ? 1.04 : 0.95, 0.87};
+    auto tiles = [&](int t) {
+        return (double)((M + kZRows[t] - 1) / kZRows[t]) * ((N + kZCols[t] - 1) / kZCols[t]) * batch;
+    };
+    if (!in_place && tiles(0) < 256) return 3;
+    int best = -1;
+    double cost = 0;
+    for (int t = 0; t < 4; ++t) {
+        if (in_place && kZRows[t] < M) continue;
+        if (t == 1 && tiles(1) < 1024) continue;  // two workgroups per CU: at least two rounds
+        const double c = tiles(t) * kZRows[t] * kZCols[t] / rate[t];
+        if (best < 0 || c < cost) {
+            best = t;
+            cost = c;
+        }
+    }
+    return best;
+}
+
+// (in place: at most 128 rows, so that some tile holds them all)
+template <bool M3>
+hipError_t launch_zgemm_tile(hipStream_t st, int tile, bool dma, int M, int N, int K, double alpha, const double *A,
+                             int64_t lda, int64_t sA, const double *B, int64_t ldb, int64_t sB, double beta, double *C,
+                             int64_t ldc, int64_t sC, int batch) {
+#define GW_ZGEMM(WM, WN, OCC, DMA)                                                                                    \
+    hipLaunchKernelGGL((k_zgemm<WM, WN, OCC, M3, DMA>), dim3((N + 32 * WN - 1) / (32 * WN),                           \
+                       (M + 32 * WM - 1) / (32 * WM), batch), dim3(256), 0, st, M, N, K, alpha, A, lda, sA, B, ldb, sB, \
+                       beta, C, ldc, sC)
+    if (!dma) GW_ZGEMM(4, 2, 2, false);
+    else if (tile == 0) GW_ZGEMM(2, 2, 3, true);
+    else if (tile == 1) GW_ZGEMM(4, 2, 2, true);
+    else if (tile == 2) GW_ZGEMM(2, 1, 5, true);
+    else GW_ZGEMM(1, 1, 8, true);
+#undef GW_ZGEMM
+    return hipGetLastError();
+}
 
 template <typename T, bool AC, bool BC, bool M3 = false>
 hipError_t launch_gemm_t(hipStream_t st, int M, int N, int K, T alpha, const T *A, int64_t lda, int64_t sA,
@@ -612,13 +854,13 @@ hipError_t launch_gemm_t(hipStream_t st, int M, int N, int K, T alpha, const T *
     constexpr bool CF32 = AC && BC && sizeof(T) == 4;
     const bool tuned = g_gemm_tile >= 0 && g_gemm_tile <= 3;
     int tile;
+    bool dma = false;
     if constexpr (Z64) {
         const bool big = M >= 256 && K >= 128;
-        // the three-product form takes 64x32 at five waves per SIMD by
-        // default, for long and thin products alike (68 TF on the LU and solve
-        // products at 2000 rows, against 65 TF for the four-product 128x32)
-        tile = big ? (tuned ? g_gemm_tile : (M3 ? 2 : 3)) : 2;
-        if (M3 && tile == 1) tile = 3;  // 128x64 with a third accumulator would spill
+        const bool in_place = (const void *)B == (const void *)C;
+        if (in_place && M > 128) return hipErrorInvalidValue;
+        tile = big && tuned ? g_gemm_tile : ztile(M, N, K, batch, in_place);
+        dma = (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15) == 0;
     } else if constexpr (CF32) {
         const bool big = M >= 256 && K >= 128;
         tile = big && tuned ? g_gemm_tile : (M >= 128 && K >= 64) ? 1 : 0;
@@ -648,7 +890,7 @@ hipError_t launch_gemm_t(hipStream_t st, int M, int N, int K, T alpha, const T *
             o.g.K = K;
             o.g.batch = batch;
             o.flops = 8.0 * M * N * (double)K * batch;
-            if (!add_eye && !C32) {
+            if (!add_eye && !C32 && (dma || !Z64)) {
                 rec->ops.push_back(std::move(o));
                 return hipSuccess;
             }
@@ -675,14 +917,14 @@ hipError_t launch_gemm_t(hipStream_t st, int M, int N, int K, T alpha, const T *
     }
     ProfScope ps(st, cls ? cls : "", flops, bytes);
 #define GW_GEMM(WM, WN, BK, OCC, XR)                                                                               \
-    hipLaunchKernelGGL((k_gemm<T, AC, BC, WM, WN, BK, OCC, XR, M3>), dim3((N + 32 * WN - 1) / (32 * WN),           \
+    hipLaunchKernelGGL((k_gemm<T, AC, BC, WM, WN, BK, OCC, XR>), dim3((N + 32 * WN - 1) / (32 * WN),               \
                        (M + 32 * WM - 1) / (32 * WM), batch), dim3(256), 0, st, M, N, K, alpha, A, lda, sA, B, ldb, \
                        sB, beta, C, ldc, sC, add_eye, C32, sC32)
-    if constexpr (Z64 || CF32) {
-        // the three-product 128x32 tile needs a third accumulator: three
-        // workgroups per CU instead of four, so that nothing spills
-        if (tile == 3) GW_GEMM(4, 1, 8, M3 ? 3 : 4, true);
-        else if (tile == 2) GW_GEMM(2, 1, 8, M3 ? 5 : 4, true);
+    if constexpr (Z64) {
+        return launch_zgemm_tile<M3>(st, tile, dma, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch);
+    } else if constexpr (CF32) {
+        if (tile == 3) GW_GEMM(4, 1, 8, 4, true);
+        else if (tile == 2) GW_GEMM(2, 1, 8, 4, true);
         else if (tile == 1) GW_GEMM(4, 2, 8, 2, false);
         else GW_GEMM(2, 2, 16, 2, false);
     } else {
@@ -723,7 +965,7 @@ hipError_t launch_zdgemm_wide(hipStream_t st, int M, int N, int K, double alpha,
                  8.0 * (double)K * N + 16.0 * (double)(mirror ? 2 * M - 1 : M) * N);
     const dim3 grid((N + 63) / 64, (M + 63) / 64, 1);
     if (mirror)
-        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2, false, true>), grid, dim3(256), 0, st, M, N, K,
+        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2, true>), grid, dim3(256), 0, st, M, N, K,
                            alpha, (const double *)A, lda, (int64_t)0, B, ldb, (int64_t)0, 0.0, (double *)C, ldc,
                            (int64_t)0, 0, (float *)nullptr, (int64_t)0);
     else
@@ -811,26 +1053,45 @@ thread_local OpRecorder *g_rec = nullptr;
 
 namespace {
 // (WM, WN, BK, OCC) of each work-queue key: the tiles and occupancies
-// launch_gemm_t picks for the product kind and tile.  The queue loop keeps a
-// few per-lane addresses live across tiles; at these occupancies the
-// three-product tiles (64x32 at five, 128x32 at three per CU) move them to
-// scratch memory, reloaded once per tile, never in the K loop.
+// launch_gemm_t picks for the product kind and tile.
 struct QShape {
     int wm, wn, bk, occ;
 };
 QShape qshape(int key) {
     const int kind = key / 4, tile = key % 4;
-    if (kind == QK_Z3M) {
-        if (tile == 2) return {2, 1, 8, 5};
-        if (tile == 0) return {2, 2, 16, 2};
-        return {4, 1, 8, 3};  // 3 (and 1, which maps to it)
+    if (kind != QK_C) {
+        if (tile == 3) return {1, 1, ZBK, 8};
+        if (tile == 2) return {2, 1, ZBK, 5};
+        if (tile == 1) return {4, 2, ZBK, 2};
+        return {2, 2, ZBK, 3};
     }
-    if (tile == 3) return {4, 1, 8, kind == QK_C ? 4 : 3};  // four-product 128x32 at four would use AGPRs
+    if (tile == 3) return {4, 1, 8, 4};
     if (tile == 2) return {2, 1, 8, 4};
     if (tile == 1) return {4, 2, 8, 2};
     return {2, 2, 16, 2};
 }
 }  // namespace
+
+// OP(T, WM, WN, BK, OCC, M3) for the kernel of a work-queue key.
+#define GW_QKEY(OP)                                             \
+    do {                                                        \
+        if (kind == QK_Z3M) {                                   \
+            if (tile == 3) OP(double, 1, 1, ZBK, 8, true);      \
+            else if (tile == 2) OP(double, 2, 1, ZBK, 5, true); \
+            else if (tile == 1) OP(double, 4, 2, ZBK, 2, true); \
+            else OP(double, 2, 2, ZBK, 3, true);                \
+        } else if (kind == QK_Z4M) {                            \
+            if (tile == 3) OP(double, 1, 1, ZBK, 8, false);     \
+            else if (tile == 2) OP(double, 2, 1, ZBK, 5, false); \
+            else if (tile == 1) OP(double, 4, 2, ZBK, 2, false); \
+            else OP(double, 2, 2, ZBK, 3, false);               \
+        } else {                                                \
+            if (tile == 3) OP(float, 4, 1, 8, 4, false);        \
+            else if (tile == 2) OP(float, 2, 1, 8, 4, false);   \
+            else if (tile == 1) OP(float, 4, 2, 8, 2, false);   \
+            else OP(float, 2, 2, 16, 2, false);                 \
+        }                                                       \
+    } while (0)
 
 int gemm_queue_occupancy(int key) {
     // workgroups of this key resident on one CU, as the runtime computes it
@@ -838,23 +1099,9 @@ int gemm_queue_occupancy(int key) {
     int occ = 0;
     hipError_t e = hipErrorInvalidValue;
     const int kind = key / 4, tile = key % 4;
-#define GW_QOCC(T, M3, WM, WN, BK, OCC) \
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gemm_queue<T, true, true, WM, WN, BK, OCC, M3>, 256, 0)
-    if (kind == QK_Z3M) {
-        if (tile == 2) GW_QOCC(double, true, 2, 1, 8, 5);
-        else if (tile == 0) GW_QOCC(double, true, 2, 2, 16, 2);
-        else GW_QOCC(double, true, 4, 1, 8, 3);
-    } else if (kind == QK_Z4M) {
-        if (tile == 3) GW_QOCC(double, false, 4, 1, 8, 3);
-        else if (tile == 2) GW_QOCC(double, false, 2, 1, 8, 4);
-        else if (tile == 1) GW_QOCC(double, false, 4, 2, 8, 2);
-        else GW_QOCC(double, false, 2, 2, 16, 2);
-    } else {
-        if (tile == 3) GW_QOCC(float, false, 4, 1, 8, 4);
-        else if (tile == 2) GW_QOCC(float, false, 2, 1, 8, 4);
-        else if (tile == 1) GW_QOCC(float, false, 4, 2, 8, 2);
-        else GW_QOCC(float, false, 2, 2, 16, 2);
-    }
+#define GW_QOCC(T, WM, WN, BK, OCC, M3) \
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gemm_queue<T, WM, WN, BK, OCC, M3>, 256, 0)
+    GW_QKEY(GW_QOCC);
 #undef GW_QOCC
     return e == hipSuccess && occ > 0 ? occ : qshape(key).occ;
 }
@@ -871,30 +1118,16 @@ hipError_t launch_gemm_queue(hipStream_t st, int key, const GemmItem *items, int
     const int kind = key / 4, tile = key % 4;
     static const char *const names[3] = {"zgemm3m_queue", "zgemm_queue", "cgemm_queue"};
     ProfScope ps(st, names[kind], flops, 0.0);
-#define GW_QGEMM(T, M3, WM, WN, BK, OCC)                                                                        \
-    do {                                                                                                         \
-        if (queue)                                                                                               \
-            hipLaunchKernelGGL((k_gemm_queue<T, true, true, WM, WN, BK, OCC, M3>), dim3(grid), dim3(256), 0, st, \
-                               items, n_items, n_tiles, queue);                                                  \
-        else                                                                                                     \
-            hipLaunchKernelGGL((k_gemm_group<T, true, true, WM, WN, BK, OCC, M3>), dim3((unsigned)n_tiles),      \
-                               dim3(256), 0, st, items, n_items, n_tiles);                                       \
+#define GW_QGEMM(T, WM, WN, BK, OCC, M3)                                                                       \
+    do {                                                                                                       \
+        if (queue)                                                                                             \
+            hipLaunchKernelGGL((k_gemm_queue<T, WM, WN, BK, OCC, M3>), dim3(grid), dim3(256), 0, st, items,    \
+                               n_items, n_tiles, queue);                                                       \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_gemm_group<T, WM, WN, BK, OCC, M3>), dim3((unsigned)n_tiles), dim3(256), 0,  \
+                               st, items, n_items, n_tiles);                                                   \
     } while (0)
-    if (kind == QK_Z3M) {
-        if (tile == 2) GW_QGEMM(double, true, 2, 1, 8, 5);
-        else if (tile == 0) GW_QGEMM(double, true, 2, 2, 16, 2);
-        else GW_QGEMM(double, true, 4, 1, 8, 3);
-    } else if (kind == QK_Z4M) {
-        if (tile == 3) GW_QGEMM(double, false, 4, 1, 8, 3);
-        else if (tile == 2) GW_QGEMM(double, false, 2, 1, 8, 4);
-        else if (tile == 1) GW_QGEMM(double, false, 4, 2, 8, 2);
-        else GW_QGEMM(double, false, 2, 2, 16, 2);
-    } else {
-        if (tile == 3) GW_QGEMM(float, false, 4, 1, 8, 4);
-        else if (tile == 2) GW_QGEMM(float, false, 2, 1, 8, 4);
-        else if (tile == 1) GW_QGEMM(float, false, 4, 2, 8, 2);
-        else GW_QGEMM(float, false, 2, 2, 16, 2);
-    }
+    GW_QKEY(GW_QGEMM);
 #undef GW_QGEMM
     return hipGetLastError();
 }

@@ -1,0 +1,77 @@
+"""W = A^-1 v at the sizes where the products and panels of the solve change
+their tile, their remainder or their variant, against LAPACK.
+
+Tolerance: Gaussian elimination with partial pivoting followed by the
+substitutions is normwise backward stable, so the relative error of W is at
+most a modest multiple of n eps cond(A); 32 n eps cond(A) allows for pivot
+growth and the three-product complex products.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+N_OMEGA = 6  # solved: j = 0 and j >= 3
+EPS = 2.0 ** -52
+
+
+def _inputs(n, seed):
+    """v symmetric positive, chi0 complex symmetric with chi0(-w) = chi0(w)*."""
+    rng = np.random.default_rng(seed)
+    b = rng.standard_normal((n, n)) / np.sqrt(n)
+    v = b @ b.T + np.eye(n)
+    chi = np.zeros((N_OMEGA, n, n), dtype=np.complex128)
+    for j in (0, 3, 4, 5):
+        c = (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) / np.sqrt(n)
+        chi[j] = c + c.T
+    for j in (1, 2):
+        chi[j] = np.conj(chi[N_OMEGA - j])
+    return v, chi
+
+
+def _check(W, v, chi):
+    n = v.shape[0]
+    for j in range(N_OMEGA):
+        A = np.eye(n) - v @ chi[j]
+        ref = np.linalg.solve(A, v.astype(np.complex128))
+        err = np.linalg.norm(W[j] - ref) / np.linalg.norm(ref)
+        assert err <= 32 * n * EPS * np.linalg.cond(A), (n, j, err)
+
+
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 16, 17, 31, 33, 63, 64, 65, 72, 96, 127, 129, 191, 193, 255, 257, 320,
+                               333, 449, 511, 513, 577, 1025])
+def test_solve_at_every_edge(n):
+    import paper_1101_2065_amd.gw as gw
+
+    v, chi = _inputs(n, 100 + n)
+    ctx = gw.Context(0)
+    vd, cd = torch.from_numpy(v).cuda(), torch.from_numpy(chi).cuda()
+    W = torch.empty_like(cd)
+    ctx.solve_W(vd, n, cd, N_OMEGA, W)
+    _check(W.cpu().numpy(), v, chi)
+    # from A, in place
+    A = torch.eye(n, dtype=torch.complex128, device="cuda") - torch.stack([vd.to(torch.complex128) @ c for c in cd])
+    ctx.solve_W_A(vd, n, A, N_OMEGA, A)
+    _check(A.cpu().numpy(), v, chi)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [5, 65, 130, 300])
+def test_solve_from_pointers_that_are_not_16_byte_aligned(n):
+    """double _Complex only asks for 8-byte alignment."""
+    import paper_1101_2065_amd.gw as gw
+
+    v, chi = _inputs(n, 7)
+    ctx = gw.Context(0)
+    size = 2 * N_OMEGA * n * n
+    bufs = [torch.zeros(size + 1, dtype=torch.float64, device="cuda") for _ in range(2)]
+    vbuf = torch.zeros(n * n + 1, dtype=torch.float64, device="cuda")
+    vbuf[1:] = torch.from_numpy(v).cuda().reshape(-1)
+    bufs[0][1:] = torch.view_as_real(torch.from_numpy(chi)).reshape(-1).cuda()
+    ctx.solve_W(vbuf.data_ptr() + 8, n, bufs[0].data_ptr() + 8, N_OMEGA, bufs[1].data_ptr() + 8)
+    W = bufs[1][1:].cpu().numpy().view(np.complex128).reshape(N_OMEGA, n, n)
+    _check(W, v, chi)
+    assert float(bufs[1][0]) == 0.0
+    ctx.close()
