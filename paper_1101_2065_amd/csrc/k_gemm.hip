@@ -16,6 +16,7 @@
 // in contiguous ranges (each XCD has its own L2).
 #include "gw_internal.h"
 #include "gw_prof.h"
+#include "k_mfma.h"
 
 #include <hip/hip_runtime.h>
 
@@ -24,27 +25,6 @@
 namespace gwk {
 
 namespace {
-
-template <typename T>
-struct Mfma;
-template <>
-struct Mfma<double> {
-    typedef double v4 __attribute__((ext_vector_type(4)));
-    static __device__ inline v4 op(double a, double b, v4 c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    // result element e of lane l is D[(l / 16) + 4 e][l % 16] (measured on gfx950)
-    static __device__ inline int row(int lane, int e) { return (lane >> 4) + 4 * e; }
-};
-template <>
-struct Mfma<float> {
-    typedef float v4 __attribute__((ext_vector_type(4)));
-    static __device__ inline v4 op(float a, float b, v4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    // result element e of lane l is D[4 (l / 16) + e][l % 16]
-    static __device__ inline int row(int lane, int e) { return 4 * (lane >> 4) + e; }
-};
 
 // C = alpha * A * B + beta * C (+ identity on the real diagonal if add_eye).
 // AC/BC: A/B complex (else real).  C is complex unless both are real.

@@ -14,10 +14,12 @@
 // same way, so every O(N^3) flop of factor and solve is an MFMA product.
 #include "gw_internal.h"
 #include "gw_prof.h"
+#include "k_mfma.h"
 
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <utility>
 
 namespace gwk {
 
@@ -45,6 +47,13 @@ template <typename T>
 __device__ inline Cx<T> crcp(Cx<T> a) {
     const T d = a.re * a.re + a.im * a.im;
     return Cx<T>{a.re / d, -a.im / d};
+}
+// Workgroup barrier that orders LDS accesses only: unlike __syncthreads it
+// does not wait for stores to global memory to land.
+__device__ __forceinline__ void lds_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#endif
 }
 
 template <typename T>
@@ -233,20 +242,39 @@ __global__ __launch_bounds__(512) void k_getf2(int n, int kb, int w, Cx<T> *A, i
 
 // Left-looking panel factorisation with the active rows in registers.
 // 512 threads; thread t owns panel rows i = t + 512 r (r < R), so the panel
-// height m = n - kb must be at most 512 R.  The 64 columns are processed in
-// chunks of BW (8 while R <= 4, else 4: registers): (1) the U rows of the
-// chunk (rows < j0) by forward substitution with the unit-lower L above it,
-// one wave per column, lane = row, each x_k broadcast from its lane once
-// final (the rows of L join an LDS copy as they become final); (2) the
-// chunk's rows >= j0 loaded into registers and updated with
-// L[:, 0:j0] U[0:j0, chunk] (left-looking: the panel's L part is read once
-// per chunk instead of being rewritten after every column); (3) the chunk
-// factorised column by column in registers (pivot = largest |re| + |im|,
-// ties to the lowest row), its row exchanges composed and applied to the
-// other panel columns in memory once per chunk; (4) written back.  At the
-// end one wave composes all 64 exchanges into a (destination, source) list
-// and the inverses of the 64x64 unit-lower L11 and upper U11 are formed in
-// registers, eight columns per wave, lane = row.
+// height m = n - kb must be at most 512 R.  What bounds it is latency: one
+// workgroup works through 64 dependent columns, so every column has a single
+// barrier and memory is only touched where its latency can be covered.
+//
+// Rows never move while the panel is factorised: a row keeps its place in
+// memory and its thread, and carries its position, which a row exchange
+// relabels.  The 64 columns are processed in chunks of BW (16 for R <= 2, 8
+// for R = 4, else 4: registers): (1) the chunk's columns are loaded; (2) its U rows (positions
+// < j0) by forward substitution with the unit-lower corner in LDS, one or two
+// columns per wave, lane = position, each x_k broadcast from its lane once final;
+// (3) the other rows are updated with L[:, 0:j0] U[0:j0, chunk]; (4) the chunk
+// is factorised column by column in registers: each wave's largest
+// |re| + |im| (ties to the lowest position) and that row go to LDS, one
+// barrier, every wave picks the largest of the eight and updates its rows with
+// it; (5) written back, without waiting for the stores: a wave reads only its
+// own rows back, in order.  Finally the rows that ended elsewhere than they began
+// are moved, once, and listed for the other columns, and the inverses of the
+// 64x64 unit-lower L11 and upper U11 are formed in registers, eight columns
+// per wave, lane = row.
+//
+// The loads of (1) and (3) go through a slab of LDS per wave, four columns of
+// its 64 rows at a time, two slabs in turn (FP64: direct copies, FP32: through
+// registers): four neighbouring lanes read 64 contiguous bytes, where a lane
+// that reads along its own row touches 64 lines per load, eight times each,
+// which the 32 KB of L1 cannot hold for eight waves; and the next slab is on
+// its way while one is used.  Within a slab, row i keeps its four values in the
+// order k ^ (i / 4) % 4, which spreads the lanes' reads over the banks.
+//
+// Measured, 256 panels of 64 columns side by side (rows moved and reloaded by
+// every chunk, five barriers and a shuffle tree per column before): 64 rows 354
+// -> 142 us, 431 rows 375 -> 250, 2000 rows about 1110 -> 830.  Of the 480k
+// cycles at 431 rows the columns take 174k (2700 each), the update 94k, the
+// chunk loads and stores 57k and 54k, the two inverses 41k.
 constexpr int GF_NT = 512;
 
 __device__ inline double rlane(double v, int k) {
@@ -257,70 +285,82 @@ __device__ inline double rlane(double v, int k) {
 __device__ inline float rlane(float v, int k) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k)); }
 __device__ inline int rlane(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
 
-// Composes the row exchanges (j, lp[j]), j in [jb, je), applied in order, into
-// (destination, source) pairs: after them, row dst holds what was row src.
-// Run by one whole wave; lane t keeps pair t in (rA, cA) and pair t + 64 in
-// (rB, cB).  Returns the number of pairs.
-__device__ inline int compose_swaps(const int *lp, int jb, int je, int lane, int &rA, int &cA, int &rB, int &cB) {
-    rA = cA = rB = cB = -1;
-    int nt = 0;
-    auto find = [&](int r) -> int {
-        const unsigned long long ma = __ballot(rA == r), mb = __ballot(rB == r);
-        if (ma) return __ffsll((long long)ma) - 1;
-        if (mb) return 64 + __ffsll((long long)mb) - 1;
-        return -1;
-    };
-    auto put = [&](int t, int r, int c) {
-        if (lane == (t & 63)) {
-            if (t < 64) {
-                rA = r;
-                cA = c;
-            } else {
-                rB = r;
-                cB = c;
+// The larger of v and the v of the lane that DPP control CTRL names; a lane
+// without one keeps its own.
+template <int CTRL>
+__device__ inline uint32_t dpp_max(uint32_t v) {
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+    return o > v ? o : v;
+}
+// Largest v over the wave.
+__device__ inline uint32_t wave_max(uint32_t v) {
+    v = dpp_max<0x111>(v);  // row_shr:1, 2, 4, 8: the last lane of each row of 16
+    v = dpp_max<0x112>(v);
+    v = dpp_max<0x114>(v);
+    v = dpp_max<0x118>(v);
+    v = dpp_max<0x142>(v);  // row_bcast:15, then :31
+    v = dpp_max<0x143>(v);
+    return (uint32_t)rlane((int)v, 63);
+}
+// Order of the pivot search in 32 bits: a row's v = |re| + |im| by its leading
+// bits (all of a float), above NaN (1) and no row at all (0).
+__device__ inline uint32_t pivot_key(double v) {
+    return v >= 0.0 ? (uint32_t)((uint64_t)__double_as_longlong(v) >> 32) + 2 : 1u;
+}
+__device__ inline uint32_t pivot_key(float v) { return v >= 0.f ? (uint32_t)__float_as_int(v) + 2 : 1u; }
+// Of the lanes in m (not empty), the one with the largest v (NaN counts as
+// none above another), ties to the smallest p.
+template <typename T>
+__device__ inline int best_of(unsigned long long m, T v, int p) {
+    int l = __ffsll((long long)m) - 1;
+    if (m & (m - 1)) {
+        T vl = rlane(v, l);
+        int pl = rlane(p, l);
+        while (m &= m - 1) {
+            const int k = __ffsll((long long)m) - 1, pk = rlane(p, k);
+            const T vk = rlane(v, k);
+            if (vk > vl || (!(vk < vl) && pk < pl)) {
+                l = k;
+                vl = vk;
+                pl = pk;
             }
         }
-    };
-    for (int j = jb; j < je; ++j) {
-        const int r1 = j, r2 = lp[j];
-        if (r1 == r2) continue;
-        int i1 = find(r1);
-        if (i1 < 0) {
-            i1 = nt++;
-            put(i1, r1, r1);
-        }
-        int i2 = find(r2);
-        if (i2 < 0) {
-            i2 = nt++;
-            put(i2, r2, r2);
-        }
-        const int c1 = rlane(i1 < 64 ? cA : cB, i1 & 63), c2 = rlane(i2 < 64 ? cA : cB, i2 & 63);
-        put(i1, r1, c2);
-        put(i2, r2, c1);
     }
-    return nt;
+    return l;
+}
+
+// f(0), ..., f(N - 1), each index a compile-time constant.
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_(std::make_integer_sequence<int, N>{}, f);
 }
 
 // GC, GI: the element types the pointers are declared with (global address
 // space for pointers read from a descriptor, so that they are not accessed as
-// flat memory).
+// flat memory).  FP64: A is 16-byte aligned.
 template <typename T, int R, int BW, typename GC = Cx<T>, typename GI = int32_t>
 __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t sA, GI *ipiv, GC *Linv, GC *Uinv,
                                             int nblk, GI *swp, GI *info, const int b) {
     constexpr int NW = GF_NT / 64;
-    static_assert(BW <= NW && NB % BW == 0, "one wave per substituted column");
-    __shared__ Cx<T> Ts[NB][NB + 1];  // the panel's top rows as they become final (padded: column reads)
-    __shared__ Cx<T> Ux[NB][BW];
-    __shared__ Cx<T> prow[BW];
-    __shared__ Cx<T> xch[2][BW];
-    __shared__ T red_v[NW];
-    __shared__ int red_i[NW];
-    __shared__ int lpiv[NB];
-    __shared__ int piv_s, zero_s, nsw_s;
-    __shared__ int sw_dst[2 * BW], sw_src[2 * BW];
-    __shared__ Cx<T> dinv[NB];
+    constexpr int KS = 4;  // columns per slab
+    constexpr int CW = (BW + NW - 1) / NW;  // substituted columns per wave
+    static_assert(NB % BW == 0 && BW % KS == 0 && BW <= 16, "whole chunks, whole slabs");
+    typedef T V2 __attribute__((ext_vector_type(2)));
+    __shared__ V2 Ts[NB][NB + 1];  // the panel's top rows as they become final (padded: column reads)
+    __shared__ V2 slab[NW][2][64 * KS];
+    __shared__ V2 Ux[NB][BW];
+    __shared__ V2 cand_row[2][NW][BW + 1];  // a wave's candidate row, and the reciprocal of its pivot
+    __shared__ T cand_v[2][NW];
+    __shared__ int cand_p[2][NW];
+    __shared__ int lpiv[NB], phys[NB];  // by column: the pivot's position then, and its row
+    __shared__ int sw_dst[2 * NB], sw_src[2 * NB], nsw;
+    __shared__ V2 dinv[NB];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     A += (int64_t)b * sA;
     ipiv += (int64_t)b * n;
     swp += (int64_t)b * SWP;
@@ -328,267 +368,416 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
     Uinv += ((int64_t)b * nblk + kb / NB) * NB * NB;
     const int m = n - kb;
     GC *P = A + (int64_t)kb * n + kb;  // panel origin, row stride n
-    const Cx<T> zero{T(0), T(0)};
+    const V2 zero{T(0), T(0)};
+
+    // value (i, c) of the panel by a 32-bit byte offset (at most 4096 rows of
+    // fewer than 64k values), so that no row keeps a 64-bit address
+    typedef dglobal<char> GB;
+    auto at = [&](int i, int c) { return (GC *)((GB *)P + ((uint32_t)i * (uint32_t)n + (uint32_t)c) * (uint32_t)sizeof(GC)); };
+    auto load = [](const GC *p) { return V2{p->re, p->im}; };
+    auto store = [](GC *p, V2 v) {
+        p->re = v.x;
+        p->im = v.y;
+    };
+    // x - l u in two fused steps per part
+    auto submul = [](V2 &x, V2 l, V2 u) {
+        x.x = fma(-l.x, u.x, x.x);
+        x.x = fma(l.y, u.y, x.x);
+        x.y = fma(-l.x, u.y, x.y);
+        x.y = fma(-l.y, u.x, x.y);
+    };
+
+    // slab q & 1: columns [c0, c0 + 4) of this wave's rows 512 r ..; rows and
+    // columns past the panel repeat its last.  FP32: staging registers, set e
+    V2 stg[sizeof(T) == 8 ? 1 : 2][sizeof(T) == 8 ? 1 : KS];
+    typedef std::integral_constant<int, 0> S0;
+    typedef std::integral_constant<int, 1> S1;
+    auto fetch = [&](int q, auto set, int r, int c0) {
+        constexpr int e = set;
+        // (opaque, so that the offsets of every row are not kept over the loop)
+        uint32_t ns = (uint32_t)n;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+s"(ns));
+#endif
+        const uint32_t r0 = (uint32_t)(64 * wave + GF_NT * r + (lane >> 2)) * ns, last = (uint32_t)(m - 1) * ns;
+        const uint32_t c = (uint32_t)min(c0 + ((lane & 3) ^ ((lane >> 4) & 3)), w - 1);
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+            const GC *g = (const GC *)((const GB *)P + (min(r0 + 16 * t * ns, last) + c) * (uint32_t)sizeof(GC));
+#if defined(__HIP_DEVICE_COMPILE__)
+            if constexpr (sizeof(T) == 8)
+                __builtin_amdgcn_global_load_lds((const dglobal<uint32_t> *)g,
+                                                 (__attribute__((address_space(3))) uint32_t *)&slab[wave][q & 1][64 * t],
+                                                 16, 0, 0);
+            else
+#endif
+                stg[sizeof(T) == 8 ? 0 : e][sizeof(T) == 8 ? 0 : t] = load(g);
+        }
+    };
+    // slab q is there and the other one has been read (next: the fetch after
+    // q's is under way and need not be waited for)
+    auto land = [&](int q, auto set, bool next) {
+        constexpr int e = set;
+        if constexpr (sizeof(T) == 8) {
+#if defined(__HIP_DEVICE_COMPILE__)
+            if (next) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+#endif
+        } else {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int t = 0; t < KS; ++t) slab[wave][q & 1][64 * t + lane] = stg[e][t];
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    auto slab_read = [&]() {  // the slab's values have arrived in registers
+#if defined(__HIP_DEVICE_COMPILE__)
+        if constexpr (sizeof(T) == 8) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#endif
+    };
+    const int swz = (lane >> 2) & 3;
+    auto slab_at = [&](int q, int k) { return slab[wave][q & 1][4 * lane + (k ^ swz)]; };
+    auto rows_here = [&](int r) { return 64 * wave + GF_NT * r < m; };
+
+    int pos[R];
+    bool row_ok[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        pos[r] = tid + GF_NT * r;
+        row_ok[r] = pos[r] < m;
+    }
+    if (tid == 0) nsw = 0;
+    // the first two slabs of a chunk's columns
+    auto fetch_chunk = [&](int j0) {
+        constexpr int H = BW / KS;
+        fetch(0, S0{}, 0, j0);
+        if (H > 1) fetch(1, S1{}, 0, j0 + KS);
+        else if (R > 1 && rows_here(1)) fetch(1, S1{}, 1, j0);
+    };
+    if (rows_here(0)) fetch_chunk(0);
 
     for (int j0 = 0; j0 < w; j0 += BW) {
         const int bw = min(BW, w - j0);
-        // (1) U rows of the chunk: x_i = a_i - sum_{k<i} L_ik x_k for i < j0.  Rows
-        // [j0 - BW, j0) became final in the previous chunk and join the staged
-        // corner; lane i keeps a_i, and x_k is broadcast from lane k once final.
-        if (j0 > 0) {
-            const int r0 = j0 - BW, nT = BW * j0, nU = j0 * bw;
-            for (int idx = tid; idx < nT + nU; idx += GF_NT) {
-                if (idx < nT) {
-                    const int i = r0 + idx / j0, k = idx % j0;
-                    Ts[i][k] = P[(int64_t)i * n + k];
-                } else {
-                    const int q = idx - nT, i = q / bw, c = q % bw;
-                    Ux[i][c] = P[(int64_t)i * n + j0 + c];
-                }
+        // (1) the chunk's columns; the first two slabs were fetched before
+        V2 a[R][BW];
+        static_for<R * (BW / KS)>([&](auto slab_no) {
+            constexpr int H = BW / KS, q = slab_no, r = q / H, h = q % H;
+            if (!rows_here(r)) {
+#pragma unroll
+                for (int k = 0; k < KS; ++k) a[r][KS * h + k] = zero;
+                return;
             }
-            __syncthreads();
+            constexpr int r1 = (q + 1) / H, r2 = (q + 2) / H;
+            typedef std::integral_constant<int, q & 1> SQ;
+            land(q, SQ{}, r1 < R && rows_here(r1));
+#pragma unroll
+            for (int k = 0; k < KS; ++k) a[r][KS * h + k] = slab_at(q, k);
+            if (r2 < R && rows_here(r2)) {
+                slab_read();
+                fetch(q, SQ{}, r2, j0 + KS * ((q + 2) % H));
+            }
+        });
+        const int nk = j0 / KS;
+        if (j0 > 0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (row_ok[r] && pos[r] < j0)
+#pragma unroll
+                    for (int c = 0; c < BW; ++c) Ux[pos[r]][c] = a[r][c];
+            lds_barrier();
+            if (rows_here(0)) fetch(0, S0{}, 0, 0);  // (3)'s first slab, beside (2)
+            // (2) x_i = a_i - sum_{k<i} L_ik x_k for positions i < j0
             if (wave < bw) {
-                const int c = wave;
-                Cx<T> x = lane < j0 ? Ux[lane][c] : zero;
+                V2 x[CW];
+#pragma unroll
+                for (int e = 0; e < CW; ++e) x[e] = lane < j0 ? Ux[lane][min(wave + NW * e, BW - 1)] : zero;
 #pragma unroll 4
                 for (int k = 0; k < j0 - 1; ++k) {
-                    const Cx<T> l = (lane > k && lane < j0) ? Ts[lane][k] : zero;
-                    const Cx<T> xk{rlane(x.re, k), rlane(x.im, k)};
-                    x.re -= l.re * xk.re - l.im * xk.im;
-                    x.im -= l.re * xk.im + l.im * xk.re;
+                    const V2 l = (lane > k && lane < j0) ? Ts[lane][k] : zero;
+#pragma unroll
+                    for (int e = 0; e < CW; ++e) submul(x[e], l, V2{rlane(x[e].x, k), rlane(x[e].y, k)});
                 }
-                if (lane < j0) {
-                    Ux[lane][c] = x;
-                    P[(int64_t)lane * n + j0 + c] = x;
-                }
-            }
-            __syncthreads();
-        }
-        // (2) rows >= j0 of the chunk into registers, left-looking update
-        Cx<T> a[R][BW];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int i = tid + GF_NT * r;
-#pragma unroll
-            for (int c = 0; c < BW; ++c) a[r][c] = zero;
-            if (i >= j0 && i < m) {
-                const GC *row = P + (int64_t)i * n;
-#pragma unroll
-                for (int c = 0; c < BW; ++c)
-                    if (c < bw) a[r][c] = row[j0 + c];
-                for (int k = 0; k < j0; ++k) {
-                    const Cx<T> l = row[k];
-#pragma unroll
-                    for (int c = 0; c < BW; ++c) {
-                        const Cx<T> u = Ux[k][c];
-                        a[r][c].re -= l.re * u.re - l.im * u.im;
-                        a[r][c].im -= l.re * u.im + l.im * u.re;
+                for (int e = 0; e < CW; ++e) {
+                    const int c = wave + NW * e;
+                    if (lane < j0 && c < bw) {
+                        Ux[lane][c] = x[e];
+                        Ts[lane][j0 + c] = x[e];
+                        store(at(phys[lane], j0 + c), x[e]);
                     }
                 }
             }
-        }
-        // (3) factor the chunk column by column; row exchanges happen in
-        // registers here and in memory (the other panel columns) once per chunk
-#pragma unroll
-        for (int c = 0; c < BW; ++c) {
-            if (c >= bw) break;
-            const int j = j0 + c;
-            T best = T(-1);
-            int bi = m;
+            lds_barrier();
+            // (3)
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const int i = tid + GF_NT * r;
-                if (i >= j && i < m) {
-                    const T v = fabs(a[r][c].re) + fabs(a[r][c].im);
-                    if (v > best) {
-                        best = v;
-                        bi = i;
+                if (!rows_here(r)) continue;
+                if constexpr (BW >= 8) {
+                    // on the matrix cores, 16 rows at a time: 16 columns as
+                    // four real products per complex one, or 8 columns as the
+                    // real product [Lr Li] [Ur Ui; -Ui Ur]
+                    typedef typename Mfma<T>::v4 v4;
+                    constexpr int NA = BW == 16 ? 2 : 1;
+                    v4 d[4][NA];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int h = 0; h < NA; ++h) d[i][h] = v4{0, 0, 0, 0};
+                    const int l15 = lane & 15, l4 = lane >> 4;
+                    for (int kb4 = 0; kb4 < nk; ++kb4) {
+                        const int q = r * nk + kb4;
+                        land(q, S0{}, false);
+                        if (kb4 + 1 < nk) fetch(q + 1, S0{}, r, KS * (kb4 + 1));
+                        else if (r + 1 < R && rows_here(r + 1)) fetch(q + 1, S0{}, r + 1, 0);
+                        const V2 u = Ux[KS * kb4 + l4][l15 & (BW - 1)];
+                        V2 l[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) l[i] = slab[wave][q & 1][4 * (16 * i + l15) + (l4 ^ ((l15 >> 2) & 3))];
+                        if constexpr (NA == 2) {
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].x, u.x, d[i][0]);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d[i][1] = Mfma<T>::op(l[i].x, u.y, d[i][1]);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].y, -u.y, d[i][0]);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d[i][1] = Mfma<T>::op(l[i].y, u.x, d[i][1]);
+                        } else {
+                            const bool im = (l15 & 8) != 0;
+                            const T b1 = im ? u.y : u.x, b2 = im ? u.x : -u.y;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].x, b1, d[i][0]);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].y, b2, d[i][0]);
+                        }
+                    }
+                    // to the rows' own threads through this wave's spare slab
+                    // (the other one may be filling): 256 / BW rows at a time,
+                    // columns permuted by row against bank conflicts
+                    const int qs = r * nk + nk - 1;
+                    constexpr int RP = 64 * KS / BW, BPP = RP / 16;
+                    V2 *sp = slab[wave][qs & 1];
+                    slab_read();
+#pragma unroll
+                    for (int p = 0; p < 64 / RP; ++p) {
+                        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                        for (int i = 0; i < BPP; ++i)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const int row = 16 * i + Mfma<T>::row(lane, e);
+                                if constexpr (NA == 2)
+                                    sp[row * BW + (l15 ^ (row & 15))] = V2{d[p * BPP + i][0][e], d[p * BPP + i][1][e]};
+                                else
+                                    ((T *)sp)[2 * (row * BW + ((l15 & 7) ^ (row & 7))) + (l15 >> 3)] =
+                                        d[p * BPP + i][0][e];
+                            }
+                        __builtin_amdgcn_wave_barrier();
+                        if (lane / RP == p) {
+                            const int row = lane % RP;
+#pragma unroll
+                            for (int c = 0; c < BW; ++c) a[r][c] -= sp[row * BW + (c ^ (row & (BW - 1)))];
+                        }
+                    }
+                } else {
+                    for (int kb4 = 0; kb4 < nk; ++kb4) {
+                        const int q = r * nk + kb4;
+                        land(q, S0{}, false);
+                        if (kb4 + 1 < nk) fetch(q + 1, S0{}, r, KS * (kb4 + 1));
+                        else if (r + 1 < R && rows_here(r + 1)) fetch(q + 1, S0{}, r + 1, 0);
+#pragma unroll
+                        for (int k = 0; k < KS; ++k) {
+                            const V2 l = slab_at(q, k);
+#pragma unroll
+                            for (int c = 0; c < BW; ++c) submul(a[r][c], l, Ux[KS * kb4 + k][c]);
+                        }
                     }
                 }
             }
-            for (int off = 32; off > 0; off >>= 1) {
-                const T ov = __shfl_xor(best, off);
-                const int oi = __shfl_xor(bi, off);
-                if (ov > best || (ov == best && oi < bi)) {
-                    best = ov;
-                    bi = oi;
+        }
+        // the next chunk's first slabs (its columns are not touched before)
+        if (j0 + BW < w && rows_here(0)) {
+            slab_read();
+            fetch_chunk(j0 + BW);
+        }
+        bool fresh[R];  // rows that this chunk factorises
+#pragma unroll
+        for (int r = 0; r < R; ++r) fresh[r] = row_ok[r] && pos[r] >= j0;
+        // (4)
+        static_for<BW>([&](auto col) {
+            constexpr int c = col;
+            if (c >= bw) return;
+            const int j = j0 + c;
+            constexpr int par = c & 1;
+            // this thread's best row, and the reciprocal its wave would publish
+            // (the division beside the search, not after it)
+            T best = T(0);
+            uint32_t key = 0;
+            int bp = 0x7fffffff;
+            V2 bx = zero;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const T v = fabs(a[r][c].x) + fabs(a[r][c].y);
+                const uint32_t kr = (row_ok[r] && pos[r] >= j) ? pivot_key(v) : 0;
+                if (kr > key || (kr == key && kr > 0 && (v > best || (!(v < best) && pos[r] < bp)))) {
+                    key = kr;
+                    best = v;
+                    bp = pos[r];
+                    bx = a[r][c];
                 }
             }
-            if (lane == 0) {
-                red_v[wave] = best;
-                red_i[wave] = bi;
+            Cx<T> rc = crcp(Cx<T>{bx.x, bx.y});
+#if defined(__HIP_DEVICE_COMPILE__)
+            asm volatile("" : "+v"(rc.re), "+v"(rc.im));  // (here, not in the candidate's branch below)
+#endif
+            const uint32_t wkey = wave_max(key);
+            if (wkey > 0) {
+                const int src = best_of(__ballot(key == wkey), best, bp);
+                if (lane == src) {
+                    cand_v[par][wave] = best;
+                    cand_p[par][wave] = bp;
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (R == 1 || pos[r] == bp)
+#pragma unroll
+                            for (int cc = c + 1; cc < BW; ++cc) cand_row[par][wave][cc] = a[r][cc];
+                    cand_row[par][wave][BW] = V2{rc.re, rc.im};
+                }
+            } else if (lane == 0) {
+                cand_p[par][wave] = -1;
             }
-            __syncthreads();
+            lds_barrier();
+            const T cv8 = cand_v[par][lane & 7];
+            const int cp8 = cand_p[par][lane & 7];
+            const uint32_t key8 = cp8 >= 0 ? pivot_key(cv8) : 0;
+            uint32_t top = dpp_max<0xB1>(key8);  // quad_perm 1 0 3 2
+            top = dpp_max<0x4E>(top);            // quad_perm 2 3 0 1
+            top = dpp_max<0x141>(top);           // row_half_mirror
+            top = (uint32_t)rlane((int)top, 0);
+            const int win = best_of(__ballot(key8 == top) & 0xffull, cv8, cp8);
+            const int piv = rlane(cp8, win);
+            const T cv = rlane(cv8, win);
+            const V2 pr = cand_row[par][win][BW];
+            V2 u[BW];
+#pragma unroll
+            for (int cc = c + 1; cc < BW; ++cc) u[cc] = cand_row[par][win][cc];
             if (tid == 0) {
-                T bv = red_v[0];
-                int bx = red_i[0];
-                for (int q = 1; q < NW; ++q)
-                    if (red_v[q] > bv || (red_v[q] == bv && red_i[q] < bx)) {
-                        bv = red_v[q];
-                        bx = red_i[q];
-                    }
-                if (bx >= m) bx = j;
-                piv_s = bx;
-                lpiv[j] = bx;
-                zero_s = (bv == T(0));
-                if (bv == T(0) && info[b] == 0) info[b] = kb + j + 1;
+                lpiv[j] = piv;
+                if (cv == T(0) && info[b] == 0) info[b] = kb + j + 1;
             }
-            __syncthreads();
-            const int piv = piv_s;
-            if (piv != j) {
+            const Cx<T> inv{pr.x, pr.y};
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int i = tid + GF_NT * r;
-                    if (i == j)
-#pragma unroll
-                        for (int cc = 0; cc < BW; ++cc) xch[0][cc] = a[r][cc];
-                    if (i == piv)
-#pragma unroll
-                        for (int cc = 0; cc < BW; ++cc) xch[1][cc] = a[r][cc];
+            for (int r = 0; r < R; ++r) {
+                if (!row_ok[r]) continue;
+                if (pos[r] == piv) {
+                    pos[r] = j;
+                    phys[j] = tid + GF_NT * r;
+                } else if (pos[r] == j) {
+                    pos[r] = piv;
                 }
-                __syncthreads();
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int i = tid + GF_NT * r;
-                    if (i == j)
-#pragma unroll
-                        for (int cc = 0; cc < BW; ++cc) a[r][cc] = xch[1][cc];
-                    if (i == piv)
-#pragma unroll
-                        for (int cc = 0; cc < BW; ++cc) a[r][cc] = xch[0][cc];
+                if (pos[r] > j && cv != T(0)) {
+                    const Cx<T> l = cmul(Cx<T>{a[r][c].x, a[r][c].y}, inv);
+                    a[r][c] = V2{l.re, l.im};
                 }
             }
 #pragma unroll
             for (int r = 0; r < R; ++r)
-                if (tid + GF_NT * r == j)
+                if (row_ok[r] && pos[r] > j && cv != T(0))
 #pragma unroll
-                    for (int cc = 0; cc < BW; ++cc) prow[cc] = a[r][cc];
-            __syncthreads();
-            if (!zero_s) {
-                const Cx<T> inv = crcp(prow[c]);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int i = tid + GF_NT * r;
-                    if (i > j && i < m) {
-                        const Cx<T> l = cmul(a[r][c], inv);
-                        a[r][c] = l;
-#pragma unroll
-                        for (int cc = 0; cc < BW; ++cc)
-                            if (cc > c) {
-                                const Cx<T> u = prow[cc];
-                                a[r][cc].re -= l.re * u.re - l.im * u.im;
-                                a[r][cc].im -= l.re * u.im + l.im * u.re;
-                            }
-                    }
-                }
-            }
-            __syncthreads();
-        }
-        // the chunk's exchanges, composed, on the panel columns outside it
-        if (wave == 0) {
-            int rA, cA, rB, cB;
-            const int nt = compose_swaps(lpiv, j0, j0 + bw, lane, rA, cA, rB, cB);
-            if (lane < nt) {
-                sw_dst[lane] = rA;
-                sw_src[lane] = cA;
-            }
-            if (lane == 0) nsw_s = nt;
-        }
-        __syncthreads();
-        {
-            const int nt = nsw_s, oc = w - bw;  // columns [0, j0) and [j0 + bw, w)
-            constexpr int MAXP = (2 * BW * NB + GF_NT - 1) / GF_NT;
-            Cx<T> v[MAXP];
-#pragma unroll
-            for (int q = 0; q < MAXP; ++q) {
-                const int idx = tid + GF_NT * q;
-                if (idx < nt * oc) {
-                    const int t = idx / oc, cc = idx % oc, col = cc < j0 ? cc : cc + bw;
-                    v[q] = P[(int64_t)sw_src[t] * n + col];
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < MAXP; ++q) {
-                const int idx = tid + GF_NT * q;
-                if (idx < nt * oc) {
-                    const int t = idx / oc, cc = idx % oc, col = cc < j0 ? cc : cc + bw;
-                    P[(int64_t)sw_dst[t] * n + col] = v[q];
-                }
-            }
-        }
-        // (4) the chunk back to memory
+                    for (int cc = c + 1; cc < BW; ++cc) submul(a[r][cc], a[r][c], u[cc]);
+        });
+        // (5)
+        uint32_t ns = (uint32_t)n;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+s"(ns));
+#endif
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int i = tid + GF_NT * r;
-            if (i >= j0 && i < m)
+            GC *row = (GC *)((GB *)P + ((uint32_t)(tid + GF_NT * r) * ns + (uint32_t)j0) * (uint32_t)sizeof(GC));
+            if (fresh[r])
 #pragma unroll
                 for (int c = 0; c < BW; ++c)
-                    if (c < bw) P[(int64_t)i * n + j0 + c] = a[r][c];
+                    if (c < bw) {
+                        store(row + c, a[r][c]);
+                        if (pos[r] < j0 + bw) Ts[pos[r]][j0 + c] = a[r][c];
+                    }
         }
-        __syncthreads();
+        lds_barrier();
+        // the new corner rows' L of the earlier chunks (stored before their
+        // waves waited for (1)'s loads, hence before this chunk's barriers)
+        for (int idx = tid; idx < bw * j0; idx += GF_NT) {
+            const int i = j0 + idx / j0, k = idx % j0;
+            Ts[i][k] = load(at(phys[i], k));
+        }
     }
 
-    if (tid < w) ipiv[kb + tid] = kb + lpiv[tid];
-    // all of the panel's exchanges as one (destination, source) list
-    if (wave == 0) {
-        int rA, cA, rB, cB;
-        const int nt = compose_swaps(lpiv, 0, w, lane, rA, cA, rB, cB);
-        if (lane == 0) swp[0] = nt;
-        if (lane < nt) {
-            swp[1 + lane] = kb + rA;
-            swp[1 + 2 * NB + lane] = kb + cA;
+    // the rows that moved: panel columns here, the others by the caller
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (row_ok[r] && pos[r] != tid + GF_NT * r) {
+            const int t = atomicAdd(&nsw, 1);  // at most 64 pivots and 64 rows they displaced
+            sw_dst[t] = pos[r];
+            sw_src[t] = tid + GF_NT * r;
         }
-        if (lane + 64 < nt) {
-            swp[1 + 64 + lane] = kb + rB;
-            swp[1 + 2 * NB + 64 + lane] = kb + cB;
+    __syncthreads();
+    {
+        const int nt = nsw;
+        constexpr int MAXP = 2 * NB * NB / GF_NT;
+        V2 v[MAXP];
+#pragma unroll
+        for (int q = 0; q < MAXP; ++q) {
+            const int idx = tid + GF_NT * q;
+            v[q] = zero;
+            if (idx < nt * w) v[q] = load(at(sw_src[idx / w], idx % w));
+        }
+        if (tid < w) ipiv[kb + tid] = kb + lpiv[tid];
+        if (tid == 0) swp[0] = nt;
+        if (tid < nt) {
+            swp[1 + tid] = kb + sw_dst[tid];
+            swp[1 + 2 * NB + tid] = kb + sw_src[tid];
+        }
+        if (tid < w) {
+            const Cx<T> d = crcp(Cx<T>{Ts[tid][tid].x, Ts[tid][tid].y});
+            dinv[tid] = V2{d.re, d.im};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < MAXP; ++q) {
+            const int idx = tid + GF_NT * q;
+            if (idx < nt * w) store(at(sw_dst[idx / w], idx % w), v[q]);
         }
     }
-    // the factored 64 x 64 corner, zero padded, and the inverses of its unit
-    // lower and upper triangles, eight columns per wave with lane = row
-    for (int idx = tid; idx < NB * NB; idx += GF_NT) {
-        const int i = idx / NB, c = idx % NB;
-        Ts[i][c] = (i < w && c < w) ? P[(int64_t)i * n + c] : zero;
-    }
-    __syncthreads();
-    if (tid < w) dinv[tid] = crcp(Ts[tid][tid]);
-    __syncthreads();
+    // the inverses of the corner's unit lower and upper triangles, eight
+    // columns per wave with lane = row; the steps before a wave's columns begin
+    // (after they end) are left out: 72 in all for every wave
     constexpr int CPW = NB / NW;
-    Cx<T> x[CPW];
+    const int c0 = wave * CPW;
+    V2 x[CPW];
 #pragma unroll
-    for (int q = 0; q < CPW; ++q) {
-        const int c = wave * CPW + q;
-        x[q] = (lane == c && c < w) ? Cx<T>{T(1), T(0)} : zero;
+    for (int q = 0; q < CPW; ++q) x[q] = (lane == c0 + q && c0 + q < w) ? V2{T(1), T(0)} : zero;
+    for (int k = c0; k < w - 1; ++k) {
+        const V2 l = (lane > k && lane < w) ? Ts[lane][k] : zero;
+#pragma unroll
+        for (int q = 0; q < CPW; ++q) submul(x[q], l, V2{rlane(x[q].x, k), rlane(x[q].y, k)});
     }
-    for (int k = 0; k < w - 1; ++k) {
-        const Cx<T> l = (lane > k && lane < w) ? Ts[lane][k] : zero;
+#pragma unroll
+    for (int q = 0; q < CPW; ++q) store(Linv + lane * NB + c0 + q, x[q]);
+#pragma unroll
+    for (int q = 0; q < CPW; ++q) x[q] = (lane == c0 + q && c0 + q < w) ? V2{T(1), T(0)} : zero;
+    for (int k = min(w, c0 + CPW) - 1; k >= 0; --k) {
+        const V2 d = dinv[k];
+        const V2 u = lane < k ? Ts[lane][k] : zero;
 #pragma unroll
         for (int q = 0; q < CPW; ++q) {
-            const Cx<T> xk{rlane(x[q].re, k), rlane(x[q].im, k)};
-            x[q].re -= l.re * xk.re - l.im * xk.im;
-            x[q].im -= l.re * xk.im + l.im * xk.re;
+            if (lane == k) {
+                const Cx<T> t = cmul(Cx<T>{x[q].x, x[q].y}, Cx<T>{d.x, d.y});
+                x[q] = V2{t.re, t.im};
+            }
+            submul(x[q], u, V2{rlane(x[q].x, k), rlane(x[q].y, k)});
         }
     }
 #pragma unroll
-    for (int q = 0; q < CPW; ++q) Linv[lane * NB + wave * CPW + q] = x[q];
-#pragma unroll
-    for (int q = 0; q < CPW; ++q) {
-        const int c = wave * CPW + q;
-        x[q] = (lane == c && c < w) ? Cx<T>{T(1), T(0)} : zero;
-    }
-    for (int k = w - 1; k >= 0; --k) {
-        const Cx<T> d = dinv[k];
-        const Cx<T> u = lane < k ? Ts[lane][k] : zero;
-#pragma unroll
-        for (int q = 0; q < CPW; ++q) {
-            if (lane == k) x[q] = cmul(x[q], d);
-            const Cx<T> xk{rlane(x[q].re, k), rlane(x[q].im, k)};
-            x[q].re -= u.re * xk.re - u.im * xk.im;
-            x[q].im -= u.re * xk.im + u.im * xk.re;
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < CPW; ++q) Uinv[lane * NB + wave * CPW + q] = x[q];
+    for (int q = 0; q < CPW; ++q) store(Uinv + lane * NB + c0 + q, x[q]);
 }
 
 template <typename T, int R, int BW>
@@ -856,18 +1045,21 @@ hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv
     int32_t *swp = (int32_t *)(scratch + (int64_t)batch * NB * n);
     hipError_t e;
     OpRecorder *rec = g_rec;
+    // the register panels copy FP64 values straight to LDS, 16 bytes each
+    const bool al = sizeof(T) == 4 || ((uintptr_t)A & 15) == 0;
     if (rec) rec->mark();
     for (int KB = 0; KB < n; KB += NBO) {
         const int WO = min(NBO, n - KB);
         for (int kb = KB; kb < KB + WO; kb += NB) {
             const int w = min(NB, n - kb);
             const int m = n - kb;
+            const bool regs = al && m <= 4096;
             if (rec) {
                 // lock-step recording: the panel (a grouped launch per
                 // register-row variant) and its row exchanges
                 RecOp o;
                 o.p = PanelItem{A, sA, ipiv, swp, info, Linv, Uinv, n, kb, w, nblk, batch, 0};
-                if (m <= 4096) {
+                if (regs) {
                     o.kind = RecOp::PANEL;
                     o.key = (m <= 512 ? 0 : m <= 1024 ? 1 : m <= 2048 ? 2 : m <= 3072 ? 3 : 4) + (sizeof(T) == 4 ? 5 : 0);
                     rec->ops.push_back(o);
@@ -887,11 +1079,14 @@ hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv
                 }
             } else {
             ProfScope ps(st, "lu_panel", 0.0, 2.0 * m * w * sizeof(Cx<T>) * (double)batch);
-            if (m <= 512)
-                hipLaunchKernelGGL((k_getf2r<T, 1, 8>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
+            if (!regs)
+                hipLaunchKernelGGL(k_getf2<T>, dim3(batch), dim3(512), 0, st, n, kb, w, A, sA, ipiv, Linv, Uinv, nblk,
+                                   scratch, swp, info);
+            else if (m <= 512)
+                hipLaunchKernelGGL((k_getf2r<T, 1, 16>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
                                    Uinv, nblk, swp, info);
             else if (m <= 1024)
-                hipLaunchKernelGGL((k_getf2r<T, 2, 8>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
+                hipLaunchKernelGGL((k_getf2r<T, 2, 16>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
                                    Uinv, nblk, swp, info);
             else if (m <= 2048)
                 hipLaunchKernelGGL((k_getf2r<T, 4, 8>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
@@ -899,12 +1094,9 @@ hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv
             else if (m <= 3072)
                 hipLaunchKernelGGL((k_getf2r<T, 6, 4>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
                                    Uinv, nblk, swp, info);
-            else if (m <= 4096)
+            else
                 hipLaunchKernelGGL((k_getf2r<T, 8, 4>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
                                    Uinv, nblk, swp, info);
-            else
-                hipLaunchKernelGGL(k_getf2<T>, dim3(batch), dim3(512), 0, st, n, kb, w, A, sA, ipiv, Linv, Uinv, nblk,
-                                   scratch, swp, info);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if (n - w > 0) {
                 ProfScope pl(st, "laswp", 0.0, 2.0 * w * (n - w) * sizeof(Cx<T>) * (double)batch);
@@ -1168,20 +1360,20 @@ hipError_t launch_c2z_set(hipStream_t st, const zflt *d, zdbl *W, int64_t n_per,
     return hipGetLastError();
 }
 
-// Panel keys: (R, BW) = (1, 8), (2, 8), (4, 8), (6, 4), (8, 4) for panels of at
+// Panel keys: (R, BW) = (1, 16), (2, 16), (4, 8), (6, 4), (8, 4) for panels of at
 // most 512, 1024, 2048, 3072, 4096 rows, complex double; +5 complex float.
 hipError_t launch_panel_group(hipStream_t st, int key, const PanelItem *items, int n_items, int64_t n_wg) {
     if (n_items <= 0 || n_wg <= 0) return hipSuccess;
     if (key < 0 || key > 9 || n_wg > INT32_MAX) return hipErrorInvalidValue;
     const dim3 grid((unsigned)n_wg), blk(GF_NT);
     switch (key) {
-        case 0: hipLaunchKernelGGL((k_getf2r_group<double, 1, 8>), grid, blk, 0, st, items, n_items); break;
-        case 1: hipLaunchKernelGGL((k_getf2r_group<double, 2, 8>), grid, blk, 0, st, items, n_items); break;
+        case 0: hipLaunchKernelGGL((k_getf2r_group<double, 1, 16>), grid, blk, 0, st, items, n_items); break;
+        case 1: hipLaunchKernelGGL((k_getf2r_group<double, 2, 16>), grid, blk, 0, st, items, n_items); break;
         case 2: hipLaunchKernelGGL((k_getf2r_group<double, 4, 8>), grid, blk, 0, st, items, n_items); break;
         case 3: hipLaunchKernelGGL((k_getf2r_group<double, 6, 4>), grid, blk, 0, st, items, n_items); break;
         case 4: hipLaunchKernelGGL((k_getf2r_group<double, 8, 4>), grid, blk, 0, st, items, n_items); break;
-        case 5: hipLaunchKernelGGL((k_getf2r_group<float, 1, 8>), grid, blk, 0, st, items, n_items); break;
-        case 6: hipLaunchKernelGGL((k_getf2r_group<float, 2, 8>), grid, blk, 0, st, items, n_items); break;
+        case 5: hipLaunchKernelGGL((k_getf2r_group<float, 1, 16>), grid, blk, 0, st, items, n_items); break;
+        case 6: hipLaunchKernelGGL((k_getf2r_group<float, 2, 16>), grid, blk, 0, st, items, n_items); break;
         case 7: hipLaunchKernelGGL((k_getf2r_group<float, 4, 8>), grid, blk, 0, st, items, n_items); break;
         case 8: hipLaunchKernelGGL((k_getf2r_group<float, 6, 4>), grid, blk, 0, st, items, n_items); break;
         default: hipLaunchKernelGGL((k_getf2r_group<float, 8, 4>), grid, blk, 0, st, items, n_items); break;
