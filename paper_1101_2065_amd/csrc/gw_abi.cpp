@@ -293,9 +293,8 @@ gw_status mixed_refine_step(gw_ctx *c, hipStream_t st, int n, const double *v, i
     GW_HIP(c, gwk::launch_rowgather_z2c(st, n, n, w.perm, w.R, nn, w.B32, nn, nb));
     GW_HIP(c, gwk::getrs_batched<zflt>(st, n, n, w.A32, nn, w.ipiv, (const zflt *)w.Li, (const zflt *)w.Ui, w.B32,
                                        nn, nb));
-    GW_HIP(c, gwk::launch_c2z_add(st, w.B32, W, nn, nb, active));
     GW_HIP(c, gwk::launch_fill_u64(st, (uint64_t *)norms, 2 * nb, 0ull));
-    GW_HIP(c, gwk::launch_norms(st, w.B32, W, nn, nb, norms));
+    GW_HIP(c, gwk::launch_add_norms(st, w.B32, W, nn, nb, active, norms));
     return GW_OK;
 }
 

@@ -227,11 +227,10 @@ hipError_t launch_conj_mirror(hipStream_t st, int64_t nn, int n_omega, zdbl *W);
 
 // Mixed precision helpers.
 hipError_t launch_z2c(hipStream_t st, const zdbl *src, zflt *dst, int64_t n);
-hipError_t launch_c2z_add(hipStream_t st, const zflt *d, zdbl *W, int64_t n_per, int batch,
-                          const int32_t *active);
-// Per-batch sum of squares into out[2*b] (|dW|^2) and out[2*b+1] (|W|^2).
-hipError_t launch_norms(hipStream_t st, const zflt *dW, const zdbl *W, int64_t n_per, int batch,
-                        double *out);
+// W += d for the active batch entries, and the sums of squares added into
+// out[2*b] (|d|^2) and out[2*b+1] (|W|^2).
+hipError_t launch_add_norms(hipStream_t st, const zflt *d, zdbl *W, int64_t n_per, int batch, const int32_t *active,
+                            double *out);
 // R = v - A W (FP64), R complex, A complex, W complex; batched.
 hipError_t launch_residual(hipStream_t st, int n, const double *v, int v_is_diag,
                            const zdbl *A, int64_t sA, const zdbl *W, int64_t sW,
