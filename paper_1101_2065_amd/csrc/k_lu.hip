@@ -277,14 +277,6 @@ __global__ __launch_bounds__(512) void k_getf2(int n, int kb, int w, Cx<T> *A, i
 // chunk loads and stores 57k and 54k, the two inverses 41k.
 constexpr int GF_NT = 512;
 
-__device__ inline double rlane(double v, int k) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, k), hi = __builtin_amdgcn_readlane((int)(b >> 32), k);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ inline float rlane(float v, int k) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k)); }
-__device__ inline int rlane(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
-
 // The larger of v and the v of the lane that DPP control CTRL names; a lane
 // without one keeps its own.
 template <int CTRL>
