@@ -73,13 +73,32 @@ __global__ __launch_bounds__(128) void k_pairvec(int n_orb, int n_occ, int n_blk
         for (int a = 0; a < NMAX; ++a)
             if (a < n) T[a] = __dadd_rn(T[a], __dmul_rn(Vs[a * n + bb], xb));
     }
-    // occupied states e0 .. e0+ecnt-1 go to columns (E - e0) * n_virt + F' of row mu
+    // occupied states e0 .. e0+ecnt-1 go to columns (E - e0) * n_virt + F' of row
+    // mu, four states at a time: a sum is one chain of additions in the fixed
+    // order, so four of them hide its latency, and the eigenvector values,
+    // uniform over the workgroup, come by scalar loads of four neighbours.
+    // 3072 products x 147k pairs: 2.8 ms (1.3 TB/s of P written) against 5.5 one
+    // state at a time with per-lane loads.
     double *Prow = P + (int64_t)mu * ldp + f - (int64_t)e0 * n_virt;
-    for (int E = e0; E < e0 + ecnt; ++E) {
+    int E = e0;
+    for (; E + 4 <= e0 + ecnt; E += 4) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int a = 0; a < NMAX; ++a)
+            if (a < n) {
+                const double *x = X + (int64_t)__builtin_amdgcn_readfirstlane(Os[a]) * n_orb + E;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = __dadd_rn(acc[q], __dmul_rn(x[q], T[a]));
+            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) Prow[(int64_t)(E + q) * n_virt] = acc[q];
+    }
+    for (; E < e0 + ecnt; ++E) {
         double acc = 0.0;
 #pragma unroll
         for (int a = 0; a < NMAX; ++a)
-            if (a < n) acc = __dadd_rn(acc, __dmul_rn(X[(int64_t)Os[a] * n_orb + E], T[a]));
+            if (a < n)
+                acc = __dadd_rn(acc, __dmul_rn(X[(int64_t)__builtin_amdgcn_readfirstlane(Os[a]) * n_orb + E], T[a]));
         Prow[(int64_t)E * n_virt] = acc;
     }
 }
