@@ -893,11 +893,16 @@ gw_status level_tables(gw_ctx *ctx, const HostMol &h, int n_orb, int n_occ, int 
 // Vertex block pairs B1 <= B2 (pb1 then pb2 in one array), grouped by tile
 // class 2 (|O1| > 16) + (|O2| > 16) with class c at class_off[c] ..
 // class_off[c+1] - 1 (class_off may be null), and the largest
-// (products x |O|^2) of a block.
-int block_pairs(const HostMol &h, int nblk, std::vector<int32_t> *pbs, int *max_vblock, int *class_off = nullptr) {
+// (products x |O|^2) of a block.  cost (or null): a pair is taken as (B2, B1)
+// where cost(B2, B1) is the smaller (a contraction whose two orders give a
+// matrix and its transpose).
+int block_pairs(const HostMol &h, int nblk, std::vector<int32_t> *pbs, int *max_vblock, int *class_off = nullptr,
+                double (*cost)(const HostMol &, int, int) = nullptr) {
     std::vector<int32_t> b1s[4], b2s[4];
-    for (int b1 = 0; b1 < nblk; ++b1)
-        for (int b2 = b1; b2 < nblk; ++b2) {
+    for (int i = 0; i < nblk; ++i)
+        for (int j = i; j < nblk; ++j) {
+            const bool swap = cost && cost(h, j, i) < cost(h, i, j);
+            const int b1 = swap ? j : i, b2 = swap ? i : j;
             const int c = 2 * (h.blk_orb[b1 + 1] - h.blk_orb[b1] > 16) + (h.blk_orb[b2 + 1] - h.blk_orb[b2] > 16);
             b1s[c].push_back(b1);
             b2s[c].push_back(b2);
@@ -918,6 +923,17 @@ int block_pairs(const HostMol &h, int nblk, std::vector<int32_t> *pbs, int *max_
         *max_vblock = std::max(*max_vblock, (h.blk_prod[b + 1] - h.blk_prod[b]) * no * no);
     }
     return npb;
+}
+
+// Operations of the self-energy contraction of a block pair at one time point:
+// per product of B1, G = sum over B2's products of gamma V, rho+- G, V rho G.
+// They grow with |O2|^2 |O1| per product of B1, so of an atom's block (40
+// products, 13 orbitals) and a bond's (16, 26) the bond's is the better B1, by
+// a factor of three.
+double sigma_pair_flops(const HostMol &h, int b1, int b2) {
+    const double n1 = h.blk_orb[b1 + 1] - h.blk_orb[b1], n2 = h.blk_orb[b2 + 1] - h.blk_orb[b2];
+    const double pm = h.blk_prod[b1 + 1] - h.blk_prod[b1], pn = h.blk_prod[b2 + 1] - h.blk_prod[b2];
+    return pm * (4.0 * pn * n2 * n2 + 16.0 * n1 * n2 * n2 + 8.0 * n1 * n1 * n2);
 }
 
 }  // namespace
@@ -1085,14 +1101,9 @@ gw_status gw_self_energy(gw_ctx *ctx, const gw_molecule *m, const double *v, con
     const int Q = L / 2 + 1;
     std::vector<int32_t> pbs;
     int max_vblock = 0, class_off[5];
-    const int npb = block_pairs(h, nblk, &pbs, &max_vblock, class_off);
+    const int npb = block_pairs(h, nblk, &pbs, &max_vblock, class_off, sigma_pair_flops);
     double cflops = 0.0;
-    for (int b1 = 0; b1 < nblk; ++b1)
-        for (int b2 = b1; b2 < nblk; ++b2) {
-            const double n1 = h.blk_orb[b1 + 1] - h.blk_orb[b1], n2 = h.blk_orb[b2 + 1] - h.blk_orb[b2];
-            const double pm = h.blk_prod[b1 + 1] - h.blk_prod[b1], pn = h.blk_prod[b2 + 1] - h.blk_prod[b2];
-            cflops += pm * (4.0 * pn * n2 * n2 + 16.0 * n1 * n2 * n2 + 8.0 * n1 * n1 * n2);
-        }
+    for (int i = 0; i < npb; ++i) cflops += sigma_pair_flops(h, pbs[i], pbs[npb + i]);
     const int64_t nn = (int64_t)n_orb * n_orb;
     const int64_t n_upper = (int64_t)n * (n + 1) / 2;
     // time points per chunk: transformed gamma and the two products within 4 GiB

@@ -130,7 +130,7 @@ __device__ inline v4d mfma4(double a, double b, v4d c) { return __builtin_amdgcn
 // f64 16x16x4 layouts (gfx950): A operand lane l = A[l % 16][l / 16], B operand
 // lane l = B[l / 16][l % 16], result element e of lane l = D[l / 16 + 4 e][l % 16].
 // TWO = false: one density only.  The wave's C+- are then added to S+-
-// (atomically; the transpose too for B1 < B2).
+// (atomically; the transpose too for two different blocks).
 template <int T1, int T2, bool TWO>
 __device__ void sigma_wave(int n1, int n2, int p1, int e1, int p2, int e2, bool same, int n_prod, int n_orb,
                            int lane, int wave, const double *__restrict__ v1, const double *v2,
@@ -262,8 +262,8 @@ __device__ void sigma_wave(int n1, int n2, int p1, int e1, int p2, int e2, bool 
 }
 
 // One workgroup (4 waves) per (time point q0 + blockIdx.x, block pair
-// B1 <= B2 of blockIdx.y); rho+- restricted to O1 x O2 are gathered into LDS
-// (zero padded to whole 16-tiles).  Rp, Rm: [2Q][n_orb^2] (Re, Im planes per
+// (B1, B2) of blockIdx.y, each unordered pair once); rho+- restricted to
+// O1 x O2 are gathered into LDS (zero padded to whole 16-tiles).  Rp, Rm: [2Q][n_orb^2] (Re, Im planes per
 // time point); Gh: [2 nq][n_upper]; S+-: [2 nq][n_orb^2].
 template <int T1, int T2, bool TWO>
 __global__ __launch_bounds__(256) void k_sigma_contract(
