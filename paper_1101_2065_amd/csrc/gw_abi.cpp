@@ -242,10 +242,30 @@ int solve_batch_max(int n, int n_omega, bool mixed, size_t budget) {
     return std::max(1, std::min(nb, n_omega / 2));
 }
 
+// A = 1 - v chi0 for nb frequencies.  The rows of v are padded to an even number
+// of values first, as the product's 16-byte copies need, in the panel scratch
+// (idle until the factorisation; 64 n values of esz bytes per frequency) where
+// that has room; else the product goes by the unaligned kernel.
+gw_status form_A(gw_ctx *c, hipStream_t st, int n, const double *v, int v_is_diag, const zdbl *chi0, int nb,
+                 SolveWs &w, zflt *A32, size_t esz) {
+    const int64_t nn = (int64_t)n * n;
+    int64_t ldv = n;
+    if (!v_is_diag && (n & 1) && (size_t)nb * 64 * esz >= 8 * (size_t)(n + 1)) {
+        ldv = n + 1;
+        GW_HIP(c, gwk::launch_pad_rows(st, n, n, v, (double *)w.scratch, ldv));
+        v = (const double *)w.scratch;
+    }
+    GW_HIP(c, gwk::launch_formA(st, n, v, ldv, v_is_diag, chi0, nn, w.A, nn, A32, nn, nb));
+    return GW_OK;
+}
+
 gw_status solve_batch_fp64(gw_ctx *c, hipStream_t st, int n, const double *v, int v_is_diag, const zdbl *chi0,
                            zdbl *W, int nb, SolveWs &w) {
     const int64_t nn = (int64_t)n * n;
-    if (chi0) GW_HIP(c, gwk::launch_formA(st, n, v, v_is_diag, chi0, nn, w.A, nn, nullptr, 0, nb));
+    if (chi0) {
+        const gw_status s = form_A(c, st, n, v, v_is_diag, chi0, nb, w, nullptr, 16);
+        if (s != GW_OK) return s;
+    }
     GW_HIP(c, gwk::launch_fill_u32(st, (uint32_t *)w.info, nb, 0u));
     GW_HIP(c, gwk::getrf_batched<zdbl>(st, n, w.A, nn, w.ipiv, (zdbl *)w.Li, (zdbl *)w.Ui, (zdbl *)w.scratch, w.info, nb));
     GW_HIP(c, gwk::launch_perm(st, n, w.ipiv, w.perm, nb));
@@ -270,8 +290,12 @@ size_t solve_ws_bytes(int n, int n_omega, bool mixed, size_t budget) {
 gw_status mixed_first_solve(gw_ctx *c, hipStream_t st, int n, const double *v, int v_is_diag, const zdbl *chi0,
                             zdbl *W, int nb, gwp::SolveWs &w) {
     const int64_t nn = (int64_t)n * n;
-    if (chi0) GW_HIP(c, gwk::launch_formA(st, n, v, v_is_diag, chi0, nn, w.A, nn, w.A32, nn, nb));
-    else GW_HIP(c, gwk::launch_z2c(st, w.A, w.A32, nn * nb));  // A given: its FP32 copy
+    if (chi0) {
+        const gw_status s = gwp::form_A(c, st, n, v, v_is_diag, chi0, nb, w, w.A32, 8);
+        if (s != GW_OK) return s;
+    } else {
+        GW_HIP(c, gwk::launch_z2c(st, w.A, w.A32, nn * nb));  // A given: its FP32 copy
+    }
     GW_HIP(c, gwk::launch_fill_u32(st, (uint32_t *)w.info, nb, 0u));
     GW_HIP(c, gwk::getrf_batched<zflt>(st, n, w.A32, nn, w.ipiv, (zflt *)w.Li, (zflt *)w.Ui, (zflt *)w.scratch, w.info,
                                        nb));
@@ -463,30 +487,55 @@ bool a_mesh_ok(int n_omega) { return !a_transform_fft() || (n_omega >= 128 && n_
 
 gw_status a_route_ws(gw_ctx *c, const std::string &pre, int n, int nhb, int n_omega, ARouteWs *w) {
     const size_t nn = (size_t)n * n;
+    w->ldd = n + (n & 1);
+    w->xs = (int64_t)nn + (a_transform_fft() ? 0 : (nn & 1));
+    const size_t dd = (size_t)n * w->ldd;
     // dense bins staged at most 2 GiB at a time (at least one bin)
-    w->dchunk = (int)std::max<size_t>(1, std::min<size_t>((size_t)std::max(1, nhb - 1), ((size_t)2 << 30) / (8 * nn)));
+    w->dchunk = (int)std::max<size_t>(1, std::min<size_t>((size_t)std::max(1, nhb - 1), ((size_t)2 << 30) / (8 * dd)));
     void *q;
     gw_status s;
-    if ((s = ws(c, pre + "aD", 8 * nn * w->dchunk, &q)) != GW_OK) return s;
+    if ((s = ws(c, pre + "aD", 8 * dd * w->dchunk, &q)) != GW_OK) return s;
     w->D = (double *)q;
-    if ((s = ws(c, pre + "aB", 8 * nn * std::max(1, nhb), &q)) != GW_OK) return s;
+    if ((s = ws(c, pre + "aB", 8 * (size_t)w->xs * std::max(1, nhb), &q)) != GW_OK) return s;
     w->B = (double *)q;
+    w->V = nullptr;
+    if (n & 1) {
+        if ((s = ws(c, pre + "aV", 8 * dd, &q)) != GW_OK) return s;
+        w->V = (double *)q;
+    }
     if ((s = ws(c, pre + "aT", 16 * (size_t)(n_omega / 2 + 1) * std::max(1, nhb), &q)) != GW_OK) return s;
     w->T = (zdbl *)q;
     return GW_OK;
 }
 
+namespace {
+// v with rows of w.ldd values: v itself, or its copy in w.V.
+gw_status v_padded(gw_ctx *ctx, hipStream_t st, int n, const double *v, const ARouteWs &w, const double **vp) {
+    *vp = v;
+    if (!w.V) return GW_OK;
+    GW_HIP(ctx, gwk::launch_pad_rows(st, n, n, v, w.V, w.ldd));
+    *vp = w.V;
+    return GW_OK;
+}
+// The products v a0 of bins [m0, m0 + cnt), expanded in w.D.
+hipError_t v_a0(hipStream_t st, int n, const double *vp, const ARouteWs &w, int m0, int cnt) {
+    return gwk::launch_dgemm(st, n, n, n, 1.0, vp, w.ldd, 0, w.D, w.ldd, n * w.ldd, 0.0, w.B + m0 * w.xs, n, w.xs, cnt);
+}
+}  // namespace
+
 gw_status a_from_bins_enqueue(gw_ctx *ctx, hipStream_t st, int n, int n_omega, int nhb, const int64_t *a_i64,
                               const int32_t *s_dev, const double *a_f64, const double *v, const ARouteWs &w,
                               const zdbl *Kt, const zdbl *tw, int j0, double domega, double eps, void *A_out) {
     // v a0 bin by bin (bins 1 .. nhb-1); its Cauchy transform is v chi0
-    const int64_t nn = (int64_t)n * n;
     const int64_t n_upper = (int64_t)n * (n + 1) / 2;
+    const double *vp;
+    gw_status s = v_padded(ctx, st, n, v, w, &vp);
+    if (s != GW_OK) return s;
     for (int m0 = 1; m0 < nhb; m0 += w.dchunk) {
         const int cnt = std::min(w.dchunk, nhb - m0);
-        if (a_i64) GW_HIP(ctx, gwk::launch_expand_bins(st, n, m0, cnt, a_i64, n_upper, s_dev, w.D));
-        else GW_HIP(ctx, gwk::launch_expand_bins(st, n, m0, cnt, a_f64, n_upper, w.D));
-        GW_HIP(ctx, gwk::launch_dgemm(st, n, n, n, 1.0, v, n, 0, w.D, n, nn, 0.0, w.B + m0 * nn, n, nn, cnt));
+        if (a_i64) GW_HIP(ctx, gwk::launch_expand_bins(st, n, m0, cnt, a_i64, n_upper, s_dev, w.D, w.ldd));
+        else GW_HIP(ctx, gwk::launch_expand_bins(st, n, m0, cnt, a_f64, n_upper, w.D, w.ldd));
+        GW_HIP(ctx, v_a0(st, n, vp, w, m0, cnt));
     }
     return a_transform_enqueue(ctx, st, n, n_omega, nhb, w, Kt, tw, j0, domega, eps, A_out);
 }
@@ -494,7 +543,7 @@ gw_status a_from_bins_enqueue(gw_ctx *ctx, hipStream_t st, int n, int n_omega, i
 gw_status a_transform_enqueue(gw_ctx *ctx, hipStream_t st, int n, int n_omega, int nhb, const ARouteWs &w,
                               const zdbl *Kt, const zdbl *tw, int j0, double domega, double eps, void *A_out) {
     if (a_transform_fft()) GW_HIP(ctx, gwk::launch_fftconv_A(st, n, n_omega, nhb, w.B, Kt, tw, (zdbl *)A_out));
-    else GW_HIP(ctx, gwk::launch_cauchy_A(st, n, n_omega, nhb, j0, domega, eps, w.B, w.T, (zdbl *)A_out));
+    else GW_HIP(ctx, gwk::launch_cauchy_A(st, n, n_omega, nhb, j0, domega, eps, w.B, w.xs, w.T, (zdbl *)A_out));
     return GW_OK;
 }
 
@@ -524,7 +573,9 @@ gw_status a_route_enqueue(gw_ctx *ctx, const BuildPlan &p, hipStream_t st, const
     // m, so bins [m0, m1) are final once the chunk with hi = m1 is done.  The
     // integer sums do not depend on their order: H is the same bit for bit.
     const int n = p.rows, nhb = p.nhb;
-    const int64_t nn = (int64_t)n * n, n_upper = (int64_t)n * (n + 1) / 2;
+    const int64_t n_upper = (int64_t)n * (n + 1) / 2;
+    const double *vp;
+    if ((s = v_padded(ctx, st, n, v, w, &vp)) != GW_OK) return s;
     // GW_HIST_CHUNKS ranges (default 4), each at most the staging buffer's bins
     int want = 4;
     if (const char *e = std::getenv("GW_HIST_CHUNKS")) want = std::max(1, std::min(64, std::atoi(e)));
@@ -548,8 +599,8 @@ gw_status a_route_enqueue(gw_ctx *ctx, const BuildPlan &p, hipStream_t st, const
     for (int c = 0; c < nch; ++c) {
         const int m0 = rg[c].m0, cnt = rg[c].cnt;
         GW_HIP(ctx, hipStreamWaitEvent(st, ctx->chunk_ev[c], 0));
-        GW_HIP(ctx, gwk::launch_expand_bins(st, n, m0, cnt, p.H, n_upper, p.sdev, w.D));
-        GW_HIP(ctx, gwk::launch_dgemm(st, n, n, n, 1.0, v, n, 0, w.D, n, nn, 0.0, w.B + m0 * nn, n, nn, cnt));
+        GW_HIP(ctx, gwk::launch_expand_bins(st, n, m0, cnt, p.H, n_upper, p.sdev, w.D, w.ldd));
+        GW_HIP(ctx, v_a0(st, n, vp, w, m0, cnt));
     }
     // st has waited for the last chunk: the second stream is joined
     return a_transform_enqueue(ctx, st, n, p.g.n_omega, nhb, w, p.Kt, p.tw, p.j0, p.dom, p.g.eps, A_out);

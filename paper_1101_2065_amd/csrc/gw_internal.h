@@ -136,12 +136,13 @@ hipError_t launch_fracbits(hipStream_t st, const uint64_t *vmax_bits, int64_t n_
 
 hipError_t launch_fill_u64(hipStream_t st, uint64_t *p, int64_t n, uint64_t value);
 // A route: A[j] = 1 - (T X)[j] for all j from the products X = v a0 of the
-// bins ([nhb][n][n] real, bin row 0 is overwritten with the identity), by one
+// bins ([nhb][n][n] real, xs values per bin; bin 0 is overwritten with the
+// identity), by one
 // complex-times-real product over the solved half of the mesh that also writes
 // the conjugate mirror (T: workspace of (n_omega/2 + 1) nhb complex), and the
 // lone point j = 0.
 hipError_t launch_cauchy_A(hipStream_t st, int n, int n_omega, int nhb, int j0, double domega, double eps,
-                           double *X, zdbl *T, zdbl *A);
+                           double *X, int64_t xs, zdbl *T, zdbl *A);
 hipError_t launch_zdgemm_wide(hipStream_t st, int M, int N, int K, double alpha, const zdbl *A, int64_t lda,
                               const double *B, int64_t ldb, zdbl *C, int64_t ldc, bool mirror);
 hipError_t launch_fill_u32(hipStream_t st, uint32_t *p, int64_t n, uint32_t value);
@@ -172,11 +173,14 @@ hipError_t launch_fftconv(hipStream_t st, int n, int n_omega, int nhb, const dou
 // chi0[j][nu][mu] = chi0[j][mu][nu] for mu < nu, all j < n_omega.
 hipError_t launch_symmetrize(hipStream_t st, int n, int n_omega, zdbl *chi0);
 // D[m - m0][mu][nu] = 2^-s H[m][t(mu, nu)] for bins m0 <= m < m0 + cnt, both
-// triangles.
+// triangles, rows of ldd >= n values.
 hipError_t launch_expand_bins(hipStream_t st, int n, int m0, int cnt, const int64_t *H, int64_t n_upper,
-                              const int32_t *s_dev, double *D);
+                              const int32_t *s_dev, double *D, int64_t ldd);
 // The same from a spectral array already in floating point.
-hipError_t launch_expand_bins(hipStream_t st, int n, int m0, int cnt, const double *a, int64_t n_upper, double *D);
+hipError_t launch_expand_bins(hipStream_t st, int n, int m0, int cnt, const double *a, int64_t n_upper, double *D,
+                              int64_t ldd);
+// dst [rows][ldd] = src [rows][cols], zero past cols.
+hipError_t launch_pad_rows(hipStream_t st, int rows, int cols, const double *src, double *dst, int64_t ldd);
 // A[j] = 1 - sum_m B[m] K_m(omega_j) for dense B[nhb][n][n] = v a0 (bins
 // m >= 1 read), every (mu, nu); 256 <= 2 n_omega <= 2048.
 hipError_t launch_fftconv_A(hipStream_t st, int n, int n_omega, int nhb, const double *B, const zdbl *Kt,
@@ -201,8 +205,8 @@ hipError_t launch_cgemm(hipStream_t st, int M, int N, int K, float alpha,
                         zflt *C, int64_t ldc, int64_t sC, int batch);
 
 // A = I - v * chi0 (v real [n][n], chi0 complex), batched over frequencies.
-// v_is_diag: v holds the diagonal only.
-hipError_t launch_formA(hipStream_t st, int n, const double *v, int v_is_diag,
+// v: rows of ldv >= n values; v_is_diag: v holds the diagonal only.
+hipError_t launch_formA(hipStream_t st, int n, const double *v, int64_t ldv, int v_is_diag,
                         const zdbl *chi0, int64_t s_chi, zdbl *A, int64_t s_A,
                         zflt *A32, int64_t s_A32, int batch);
 

@@ -70,10 +70,14 @@ gw_status build_enqueue(gw_ctx *c, const BuildPlan &p, hipStream_t st, void *chi
 // A = 1 - v chi0 formed from v a0: the products v a0 of every bin (B, bins
 // >= 1; row 0 takes the identity), the dense bins of one chunk (D, dchunk
 // bins) and the Cauchy-transform matrix T of the solved half of the mesh.
+// Rows are padded to an even number of values (ldd per row of D, xs per bin of
+// B), which the products' 16-byte copies need; V: room for v with rows of ldd
+// values, null for an even n.
 struct ARouteWs {
-    double *D = nullptr, *B = nullptr;
+    double *D = nullptr, *B = nullptr, *V = nullptr;
     zdbl *T = nullptr;
     int dchunk = 1;
+    int64_t ldd = 0, xs = 0;
 };
 // GW_A_TRANSFORM=fft: the A route's transform by FFT convolution (meshes of
 // 128 to 1024 points) instead of the matrix product (any mesh).

@@ -540,7 +540,7 @@ __global__ __launch_bounds__(256) void k_symmetrize(int n, int n_omega, int nt, 
 template <typename HT>
 __global__ __launch_bounds__(256) void k_expand_bins(int n, int nt, const HT *__restrict__ H, int64_t n_upper,
                                                      const int32_t *__restrict__ s_dev, int m0,
-                                                     double *__restrict__ D) {
+                                                     double *__restrict__ D, int64_t ldd) {
     __shared__ double t[32][33];
     int tile = blockIdx.x, bi = 0;
     while (tile >= nt - bi) {
@@ -549,9 +549,8 @@ __global__ __launch_bounds__(256) void k_expand_bins(int n, int nt, const HT *__
     }
     const int bj = bi + tile;
     const int s = s_dev ? *s_dev : 0;
-    const int64_t nn = (int64_t)n * n;
     const HT *Hm = H + ((int64_t)m0 + blockIdx.y) * n_upper;
-    double *Dm = D + (int64_t)blockIdx.y * nn;
+    double *Dm = D + (int64_t)blockIdx.y * n * ldd;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -560,7 +559,7 @@ __global__ __launch_bounds__(256) void k_expand_bins(int n, int nt, const HT *__
         if (r < n && c < n && c >= r) {
             const int64_t tr = (int64_t)r * n - ((int64_t)r * (r - 1)) / 2 - r;
             val = hval(Hm, tr + c, s);
-            Dm[(int64_t)r * n + c] = val;
+            Dm[r * ldd + c] = val;
         }
         t[ty + 8 * q][tx] = val;
     }
@@ -568,7 +567,7 @@ __global__ __launch_bounds__(256) void k_expand_bins(int n, int nt, const HT *__
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int r = bj * 32 + ty + 8 * q, c = bi * 32 + tx;  // lower (r, c) = upper (c, r)
-        if (r < n && c < n && r > c) Dm[(int64_t)r * n + c] = t[tx][ty + 8 * q];
+        if (r < n && c < n && r > c) Dm[r * ldd + c] = t[tx][ty + 8 * q];
     }
 }
 
@@ -577,24 +576,40 @@ __global__ __launch_bounds__(256) void k_expand_bins(int n, int nt, const HT *__
 namespace {
 template <typename HT>
 hipError_t expand_bins_impl(hipStream_t st, int n, int m0, int cnt, const HT *H, int64_t n_upper,
-                            const int32_t *s_dev, double *D) {
+                            const int32_t *s_dev, double *D, int64_t ldd) {
     if (cnt < 1) return hipSuccess;
     if (cnt > 65535 || m0 < 0) return hipErrorInvalidValue;
     const int nt = (n + 31) / 32;
     ProfScope pm(st, "expand_bins", 0.0, (8.0 * cnt) * ((double)n * (n + 1) / 2 + (double)n * n));
     hipLaunchKernelGGL((k_expand_bins<HT>), dim3((unsigned)(nt * (nt + 1) / 2), (unsigned)cnt), dim3(256), 0, st, n,
-                       nt, H, n_upper, s_dev, m0, D);
+                       nt, H, n_upper, s_dev, m0, D, ldd);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_expand_bins(hipStream_t st, int n, int m0, int cnt, const int64_t *H, int64_t n_upper,
-                              const int32_t *s_dev, double *D) {
-    return expand_bins_impl(st, n, m0, cnt, H, n_upper, s_dev, D);
+                              const int32_t *s_dev, double *D, int64_t ldd) {
+    return expand_bins_impl(st, n, m0, cnt, H, n_upper, s_dev, D, ldd);
 }
 
-hipError_t launch_expand_bins(hipStream_t st, int n, int m0, int cnt, const double *a, int64_t n_upper, double *D) {
-    return expand_bins_impl(st, n, m0, cnt, a, n_upper, (const int32_t *)nullptr, D);
+hipError_t launch_expand_bins(hipStream_t st, int n, int m0, int cnt, const double *a, int64_t n_upper, double *D,
+                              int64_t ldd) {
+    return expand_bins_impl(st, n, m0, cnt, a, n_upper, (const int32_t *)nullptr, D, ldd);
+}
+
+namespace {
+__global__ void k_pad_rows(int rows, int cols, const double *__restrict__ src, double *__restrict__ dst, int64_t ldd) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= ldd) return;
+    for (int r = blockIdx.y; r < rows; r += gridDim.y) dst[r * ldd + c] = c < cols ? src[(int64_t)r * cols + c] : 0.0;
+}
+}  // namespace
+
+hipError_t launch_pad_rows(hipStream_t st, int rows, int cols, const double *src, double *dst, int64_t ldd) {
+    GW_DEFER(launch_pad_rows(st, rows, cols, src, dst, ldd));
+    hipLaunchKernelGGL(k_pad_rows, dim3((unsigned)((ldd + 255) / 256), (unsigned)std::min(rows, 65535)), dim3(256), 0,
+                       st, rows, cols, src, dst, ldd);
+    return hipGetLastError();
 }
 
 hipError_t launch_fftconv_A(hipStream_t st, int n, int n_omega, int nhb, const double *B, const zdbl *Kt,
@@ -654,7 +669,8 @@ __global__ void k_eye_row(int n, int64_t nn, double *__restrict__ X0) {
 // A[0][e] = -sum_q T'[0][q] X[q][e], one entry per thread, rows of X read
 // coalesced.
 __global__ __launch_bounds__(256) void k_cauchy_row0(int64_t nn, int nhb, const zdbl *__restrict__ T0,
-                                                     const double *__restrict__ X, zdbl *__restrict__ A0) {
+                                                     const double *__restrict__ X, int64_t xs,
+                                                     zdbl *__restrict__ A0) {
     extern __shared__ zdbl t0[];
     for (int q = threadIdx.x; q < nhb; q += blockDim.x) t0[q] = T0[q];
     __syncthreads();
@@ -662,7 +678,7 @@ __global__ __launch_bounds__(256) void k_cauchy_row0(int64_t nn, int nhb, const 
     if (e >= nn) return;
     double re = 0.0, im = 0.0;
     for (int q = 0; q < nhb; ++q) {
-        const double x = X[(int64_t)q * nn + e];
+        const double x = X[q * xs + e];
         re = fma(t0[q].re, x, re);
         im = fma(t0[q].im, x, im);
     }
@@ -670,7 +686,7 @@ __global__ __launch_bounds__(256) void k_cauchy_row0(int64_t nn, int nhb, const 
 }
 
 hipError_t launch_cauchy_A(hipStream_t st, int n, int n_omega, int nhb, int j0, double domega, double eps,
-                           double *X, zdbl *T, zdbl *A) {
+                           double *X, int64_t xs, zdbl *T, zdbl *A) {
     const int64_t nn = (int64_t)n * n;
     const int half = n_omega / 2;
     hipLaunchKernelGGL(k_cauchy_T, dim3((nhb + 255) / 256, half + 1), dim3(256), 0, st, n_omega, j0, domega, eps, nhb,
@@ -682,13 +698,13 @@ hipError_t launch_cauchy_A(hipStream_t st, int n, int n_omega, int nhb, int j0, 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the solved half j = n_omega/2 .. n_omega-1 in one product, which also
     // writes the other half by A(-omega) = A(omega)* (v real)
-    if ((e = launch_zdgemm_wide(st, half, (int)nn, nhb, -1.0, T + nhb, nhb, X, nn, A + (int64_t)half * nn, nn,
+    if ((e = launch_zdgemm_wide(st, half, (int)nn, nhb, -1.0, T + nhb, nhb, X, xs, A + (int64_t)half * nn, nn,
                                 true)) != hipSuccess)
         return e;
     {
         ProfScope ps(st, "cauchy_row0", 4.0 * (double)nn * nhb, 8.0 * (double)nn * nhb + 16.0 * (double)nn);
         hipLaunchKernelGGL(k_cauchy_row0, dim3((unsigned)((nn + 255) / 256)), dim3(256), sizeof(zdbl) * nhb, st, nn,
-                           nhb, T, X, A);
+                           nhb, T, X, xs, A);
         return hipGetLastError();
     }
 }

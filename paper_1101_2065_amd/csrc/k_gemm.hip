@@ -477,6 +477,228 @@ __global__ __launch_bounds__(256, OCC) void k_zgemm(int M, int N, int K, double 
                                 (int)(t % gx) * 32 * WN);
 }
 
+// ------------------------------------------------------------------ real FP64 products
+// The same scheme for a real B, whose 16-byte copies carry two neighbouring
+// columns (the MFMA's 16 columns are then every second one of 32), and
+//   AC = false: a real A, whose copies carry two neighbouring k.  K advances 16
+//     (8 for 128x128); within each 8 the matrix cores take k = 0 2 4 6, then
+//     1 3 5 7.  A complex B is a real one with twice the columns.
+//   AC = true: a complex A as in zgemm_tile, K advances 8.
+// The copies need 16-byte aligned rows: even leading dimensions, and for an odd
+// N a row of B that can be read one value past it (ldb > N).  MIR: row r >= 1
+// of C is also written, conjugated, r rows before C's first row (C(-omega) =
+// C(omega)* for a C whose rows are omega_r on a symmetric mesh starting at
+// omega = 0).
+//
+// Measured against the tile staged through registers (gemm_tile), real A:
+// 2000^3 x 24: 128x128 68.0 TF, 128x64 65.9, 64x64 60.3, staged 54.9;
+// 1104 x 2208 x 1104 x 24: 61.7, 64.5, 61.6, staged 54.2.  The Cauchy product
+// (512 x 4e6 x 192) gains little, 33.4 -> 32.4 ms: it writes 65 GB.
+template <bool AC, int WM, int WN, int BK, bool MIR>
+__device__ __forceinline__ void rgemm_tile(int M, int N, int K, double alpha, const dglobal<double> *A, int64_t lda,
+                                           const dglobal<double> *B, int64_t ldb, double beta, dglobal<double> *C,
+                                           int64_t ldc, int add_eye, float *C32, int m0, int n0) {
+    typedef Mfma<double>::v4 v4;
+    typedef dglobal<zd2u> G2;
+    typedef dglobal<double> GD;
+    constexpr int BM = 32 * WM, BN = 32 * WN, WP = WN / 2;
+    constexpr int KA = AC ? 4 : 8;               // k per chunk of A
+    constexpr int CA = BM / 16 * (BK / KA);      // chunks of 64 16-byte values per stage
+    constexpr int CB = BN / 32 * (BK / 4);       // (B: 4 k x 32 columns)
+    constexpr int NA = CA / 4, NB4 = CB / 4;     // copied by each wave
+    constexpr int NP = AC ? 2 : 1;               // real and imaginary part of C
+    static_assert(WN % 2 == 0 && CA % 4 == 0 && CB % 4 == 0, "whole chunks per wave");
+    __shared__ zd2 lds[2][(CA + CB) * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    // this lane's value of a chunk of A (rows as in zgemm_tile) ...
+    const int ar = lane >> 2, aq = (lane & 3) ^ ((lane >> 4) & 3);
+    auto a_at = [&](int c, int &row, int &k) {
+        row = m0 + (c / (BK / KA)) * 16 + ar;
+        k = (c % (BK / KA)) * KA + (AC ? aq : 2 * aq);
+    };
+    // ... and of B: chunk c holds the k of step c / (BN / 32): for a real A the
+    // even or the odd k of an 8
+    auto b_at = [&](int c, int &k, int &col) {
+        const int st = c / (BN / 32);
+        k = AC ? 4 * st + (lane >> 4) : 8 * (st >> 1) + 2 * (lane >> 4) + (st & 1);
+        col = n0 + (c % (BN / 32)) * 32 + 2 * (lane & 15);
+    };
+    const GD *pa[NA], *pb[NB4];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        int row, k;
+        a_at(wave * NA + i, row, k);
+        pa[i] = A + ((int64_t)min(row, M - 1) * lda + k) * (AC ? 2 : 1);
+    }
+#pragma unroll
+    for (int i = 0; i < NB4; ++i) {
+        int k, col;
+        b_at(wave * NB4 + i, k, col);
+        pb[i] = B + (int64_t)k * ldb + min(col, (N - 1) & ~1);
+    }
+    v4 acc[NP][WM][WN];
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j) acc[p][i][j] = v4{0, 0, 0, 0};
+    auto stage = [&](int s) {
+        zd2 *base = lds[s];
+#if defined(__HIP_DEVICE_COMPILE__)
+        typedef __attribute__((address_space(3))) uint32_t L;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            __builtin_amdgcn_global_load_lds((const dglobal<uint32_t> *)pa[i], (L *)(base + (wave * NA + i) * 64), 16,
+                                             0, 0);
+            pa[i] += BK * (AC ? 2 : 1);
+        }
+#pragma unroll
+        for (int i = 0; i < NB4; ++i) {
+            __builtin_amdgcn_global_load_lds((const dglobal<uint32_t> *)pb[i], (L *)(base + (CA + wave * NB4 + i) * 64),
+                                             16, 0, 0);
+            pb[i] += BK * ldb;
+        }
+#endif
+    };
+    const int fa = 4 * (lane & 15) + ((lane >> 4) ^ ((lane >> 2) & 3));
+    auto compute = [&](int s) {
+        const zd2 *base = lds[s];
+#pragma unroll
+        for (int q = 0; q < BK / KA; ++q) {
+            zd2 a[WM];
+#pragma unroll
+            for (int i = 0; i < WM; ++i) a[i] = base[((wm * WM + i) * (BK / KA) + q) * 64 + fa];
+#pragma unroll
+            for (int t = 0; t < KA / 4; ++t) {
+                zd2 b[WP];
+#pragma unroll
+                for (int j = 0; j < WP; ++j)
+                    b[j] = base[(CA + (q * (KA / 4) + t) * (BN / 32) + wn * WP + j) * 64 + lane];
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+#pragma unroll
+                    for (int i = 0; i < WM; ++i) {
+                        const double x = (AC ? p : t) ? a[i].y : a[i].x;
+#pragma unroll
+                        for (int j = 0; j < WP; ++j) {
+                            acc[p][i][2 * j] = Mfma<double>::op(x, b[j].x, acc[p][i][2 * j]);
+                            acc[p][i][2 * j + 1] = Mfma<double>::op(x, b[j].y, acc[p][i][2 * j + 1]);
+                        }
+                    }
+            }
+        }
+    };
+    const int nfull = K / BK;
+    if (nfull > 0) stage(0);
+    int cur = 0;
+    for (int k = 0; k < nfull; ++k) {
+        copies_done_barrier();
+        if (k + 1 < nfull) stage(cur ^ 1);
+        compute(cur);
+        cur ^= 1;
+    }
+    if (nfull * BK < K) {
+        // the last, partial step: zeros past K, into the buffer nobody reads
+        const int left = K - nfull * BK;
+        zd2 *base = lds[cur];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            int row, k;
+            a_at(wave * NA + i, row, k);
+            zd2 x{0, 0};
+            if (k < left) {
+                x.x = pa[i][0];
+                if (AC || k + 1 < left) x.y = pa[i][1];
+            }
+            base[(wave * NA + i) * 64 + lane] = x;
+        }
+#pragma unroll
+        for (int i = 0; i < NB4; ++i) {
+            int k, col;
+            b_at(wave * NB4 + i, k, col);
+            zd2 x{0, 0};
+            if (k < left) {
+                x.x = pb[i][0];
+                if (col + 1 < N) x.y = pb[i][1];
+            }
+            base[(CA + wave * NB4 + i) * 64 + lane] = x;
+        }
+        copies_done_barrier();
+        compute(cur);
+    }
+    // every read of A and B is done before C, which may be one of them, is written
+    copies_done_barrier();
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WP; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = m0 + (wm * WM + i) * 16 + Mfma<double>::row(lane, e);
+                const int col = n0 + (wn * WP + j) * 32 + 2 * (lane & 15);
+                if (row >= M || col >= N) continue;
+                if constexpr (AC) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (col + h >= N) continue;
+                        G2 *pc = (G2 *)C + (int64_t)row * ldc + col + h;
+                        zd2 v{alpha * acc[0][i][2 * j + h][e], alpha * acc[NP - 1][i][2 * j + h][e]};
+                        if (beta != 0.0) {
+                            const zd2 c = *pc;
+                            v.x += beta * c.x;
+                            v.y += beta * c.y;
+                        }
+                        *pc = v;
+                        if (MIR && row >= 1) *((G2 *)C + (col + h - (int64_t)row * ldc)) = zd2{v.x, -v.y};
+                    }
+                } else {
+                    GD *pc = C + (int64_t)row * ldc + col;
+                    zd2 v{alpha * acc[0][i][2 * j][e], alpha * acc[0][i][2 * j + 1][e]};
+                    const bool two = col + 1 < N;
+                    if (beta != 0.0) {
+                        v.x += beta * pc[0];
+                        if (two) v.y += beta * pc[1];
+                    }
+                    if (add_eye && col == 2 * row) v.x += 1.0;  // complex C: its real diagonal
+                    if (two) *(G2 *)pc = v;
+                    else pc[0] = v.x;
+                    if (C32) {
+                        float *q = C32 + (int64_t)row * ldc + col;
+                        q[0] = (float)v.x;
+                        if (two) q[1] = (float)v.y;
+                    }
+                }
+            }
+}
+
+// BYCOL: tiles column band by column band (for a B much larger than A: each
+// slice of B is read from HBM once), else row band by row band.
+template <bool AC, int WM, int WN, int BK, int OCC, bool BYCOL, bool MIR>
+__global__ __launch_bounds__(256, OCC) void k_rgemm(int M, int N, int K, double alpha, const double *A, int64_t lda,
+                                                    int64_t sA, const double *B, int64_t ldb, int64_t sB, double beta,
+                                                    double *C, int64_t ldc, int64_t sC, int add_eye, float *C32,
+                                                    int64_t sC32) {
+    const int gx = gridDim.x, gy = gridDim.y;
+    const int64_t nt = (int64_t)gx * gy * gridDim.z;
+    const int64_t l = blockIdx.x + (int64_t)gx * (blockIdx.y + (int64_t)gy * blockIdx.z);
+    const int64_t n8 = nt / 8, t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;
+    const int64_t bz = t / ((int64_t)gx * gy);
+    const int by = (int)(BYCOL ? t % gy : (t / gx) % gy), bx = (int)(BYCOL ? (t / gy) % gx : t % gx);
+    constexpr int e = AC ? 2 : 1;
+    rgemm_tile<AC, WM, WN, BK, MIR>(M, N, K, alpha, (const dglobal<double> *)A + bz * sA * e, lda,
+                                    (const dglobal<double> *)B + bz * sB, ldb, beta,
+                                    (dglobal<double> *)C + bz * sC * e, ldc, add_eye, C32 ? C32 + bz * sC32 : nullptr,
+                                    by * 32 * WM, bx * 32 * WN);
+}
+
+// Whether rgemm_tile can take these operands (see there).
+bool rgemm_ok(int N, const void *A, int64_t lda, int64_t sA, bool ac, const void *B, int64_t ldb, int64_t sB) {
+    const bool a_even = ac || ((lda | sA) & 1) == 0;
+    return (((uintptr_t)A | (uintptr_t)B) & 15) == 0 && a_even && ((ldb | sB) & 1) == 0 && ((N & 1) == 0 || ldb > N);
+}
+
 // XR: tile order.  0: as launched; 1 and 2: workgroups are dealt to the
 // eight XCDs in turn, each with its own L2, so each XCD gets a contiguous
 // range of tiles, row band by row band (1: tiles sharing an A row band share
@@ -807,6 +1029,42 @@ int ztile(int M, int N, int K, int batch, bool in_place) {
     return best;
 }
 
+// A real-B product by rgemm_tile (rgemm_ok): the tile of the least padded area
+// over its rate (see there; the 128-wide ones need two rounds of two workgroups
+// per CU to show theirs).
+template <bool AC>
+hipError_t launch_rgemm(hipStream_t st, int M, int N, int K, double alpha, const double *A, int64_t lda, int64_t sA,
+                        const double *B, int64_t ldb, int64_t sB, double beta, double *C, int64_t ldc, int64_t sC,
+                        int batch, int add_eye, float *C32, int64_t sC32) {
+    const int bm[3] = {64, 128, 128}, bn[3] = {64, 64, 128};
+    const double rate[3] = {1.0, 1.05, AC ? 0.0 : 1.08};
+    int tile = 0;
+    double cost = 0;
+    for (int t = 0; t < 3; ++t) {
+        if (rate[t] == 0) continue;
+        const double tiles = (double)((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]) * batch;
+        const double c = tiles * bm[t] * bn[t] / rate[t];
+        if (t == 0 || (c < cost && tiles >= 1024)) {
+            tile = t;
+            cost = c;
+        }
+    }
+#define GW_RGEMM(WM, WN, BK, OCC)                                                                                 \
+    hipLaunchKernelGGL((k_rgemm<AC, WM, WN, BK, OCC, false, false>), dim3((N + 32 * WN - 1) / (32 * WN),          \
+                       (M + 32 * WM - 1) / (32 * WM), batch), dim3(256), 0, st, M, N, K, alpha, A, lda, sA, B, ldb, \
+                       sB, beta, C, ldc, sC, add_eye, C32, sC32)
+    if constexpr (AC) {
+        if (tile == 1) GW_RGEMM(4, 2, 8, 2);
+        else GW_RGEMM(2, 2, 8, 3);
+    } else {
+        if (tile == 2) GW_RGEMM(4, 4, 8, 2);
+        else if (tile == 1) GW_RGEMM(4, 2, 16, 2);
+        else GW_RGEMM(2, 2, 16, 3);
+    }
+#undef GW_RGEMM
+    return hipGetLastError();
+}
+
 // (in place: at most 128 rows, so that some tile holds them all)
 template <bool M3>
 hipError_t launch_zgemm_tile(hipStream_t st, int tile, bool dma, int M, int N, int K, double alpha, const double *A,
@@ -908,8 +1166,13 @@ hipError_t launch_gemm_t(hipStream_t st, int M, int N, int K, T alpha, const T *
         else if (tile == 1) GW_GEMM(4, 2, 8, 2, false);
         else GW_GEMM(2, 2, 16, 2, false);
     } else {
-        if (tile == 1) GW_GEMM(4, 2, 8, 2, false);
-        else GW_GEMM(2, 2, 16, 2, false);
+        static_assert(sizeof(T) == 8, "real operands in FP64 only");
+        // real A, complex B: a real product with twice the columns
+        constexpr int eb = BC ? 2 : 1;
+        if (rgemm_ok(N * eb, A, lda, sA, AC, B, ldb * eb, sB * eb))
+            return launch_rgemm<AC>(st, M, N * eb, K, alpha, A, lda, sA, B, ldb * eb, sB * eb, beta, C, ldc * eb,
+                                    sC * eb, batch, add_eye, C32, sC32 * 2);
+        GW_GEMM(2, 2, 16, 2, false);
     }
 #undef GW_GEMM
     return hipGetLastError();
@@ -943,15 +1206,27 @@ hipError_t launch_zdgemm_wide(hipStream_t st, int M, int N, int K, double alpha,
     if (M <= 0 || N <= 0) return hipSuccess;
     ProfScope ps(st, "cauchy_gemm", 4.0 * M * (double)N * K,
                  8.0 * (double)K * N + 16.0 * (double)(mirror ? 2 * M - 1 : M) * N);
+    const double *A_ = (const double *)A;
+    double *C_ = (double *)C;
+    const int64_t z = 0;
+    float *none = nullptr;
+    if (rgemm_ok(N, A, lda, 0, true, B, ldb, 0)) {
+        const dim3 grid((N + 63) / 64, (M + 127) / 128, 1);
+        if (mirror)
+            hipLaunchKernelGGL((k_rgemm<true, 4, 2, 8, 2, true, true>), grid, dim3(256), 0, st, M, N, K, alpha, A_, lda,
+                               z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
+        else
+            hipLaunchKernelGGL((k_rgemm<true, 4, 2, 8, 2, true, false>), grid, dim3(256), 0, st, M, N, K, alpha, A_,
+                               lda, z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
+        return hipGetLastError();
+    }
     const dim3 grid((N + 63) / 64, (M + 63) / 64, 1);
     if (mirror)
-        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2, true>), grid, dim3(256), 0, st, M, N, K,
-                           alpha, (const double *)A, lda, (int64_t)0, B, ldb, (int64_t)0, 0.0, (double *)C, ldc,
-                           (int64_t)0, 0, (float *)nullptr, (int64_t)0);
+        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2, true>), grid, dim3(256), 0, st, M, N, K, alpha,
+                           A_, lda, z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
     else
-        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2>), grid, dim3(256), 0, st, M, N, K, alpha,
-                           (const double *)A, lda, (int64_t)0, B, ldb, (int64_t)0, 0.0, (double *)C, ldc, (int64_t)0,
-                           0, (float *)nullptr, (int64_t)0);
+        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2>), grid, dim3(256), 0, st, M, N, K, alpha, A_,
+                           lda, z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
     return hipGetLastError();
 }
 
@@ -988,17 +1263,18 @@ hipError_t launch_cgemm(hipStream_t st, int M, int N, int K, float alpha, const 
                                             beta, (float *)C, ldc, sC, batch);
 }
 
-hipError_t launch_formA(hipStream_t st, int n, const double *v, int v_is_diag, const zdbl *chi0, int64_t s_chi,
+hipError_t launch_formA(hipStream_t st, int n, const double *v, int64_t ldv, int v_is_diag, const zdbl *chi0,
+                        int64_t s_chi,
                         zdbl *A, int64_t s_A, zflt *A32, int64_t s_A32, int batch) {
     if (v_is_diag) {
-        GW_DEFER(launch_formA(st, n, v, v_is_diag, chi0, s_chi, A, s_A, A32, s_A32, batch));
+        GW_DEFER(launch_formA(st, n, v, ldv, v_is_diag, chi0, s_chi, A, s_A, A32, s_A32, batch));
         const int xb = (n + 255) / 256, zb = std::min(batch, 65535);
         dim3 grid((unsigned)xb, (unsigned)std::max(1, std::min(n, 65536 / std::max(1, xb * zb))), (unsigned)zb);
         hipLaunchKernelGGL(k_formA_diag, grid, dim3(256), 0, st, n, batch, v, chi0, s_chi, A, s_A, A32, s_A32);
         return hipGetLastError();
     }
     // A = -v * chi0 + 1 (v real, shared by the batch: batch stride 0)
-    return launch_gemm_t<double, false, true>(st, n, n, n, -1.0, v, n, 0, (const double *)chi0, n, s_chi, 0.0,
+    return launch_gemm_t<double, false, true>(st, n, n, n, -1.0, v, ldv, 0, (const double *)chi0, n, s_chi, 0.0,
                                               (double *)A, n, s_A, batch, 1, (float *)A32, s_A32);
 }
 

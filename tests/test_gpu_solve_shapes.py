@@ -75,3 +75,29 @@ def test_solve_from_pointers_that_are_not_16_byte_aligned(n):
     _check(W, v, chi)
     assert float(bufs[1][0]) == 0.0
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 65, 97, 128, 129, 161, 255, 300])
+@pytest.mark.parametrize("bins", [2, 5, 64])
+def test_spectral_products_at_every_edge(n, bins):
+    """A = 1 - v chi0 by both routes on one small molecule whose basis is cut at
+    n: the products v a0 and the Cauchy product (odd and even rows, K tails)
+    must give 1 - v chi0.  Both sum the same terms in another order: at most
+    (n + bins) roundings of entries bounded by |v| |a0| |T|, so 8 (n + bins) eps
+    times the largest entry of |v| |chi0| + 1."""
+    import gw_synth as gs
+    import paper_1101_2065_amd.gw as gw
+
+    mol = gs.truncate_products(gs.chain_molecule(6, 11), n)
+    N, top = {2: (16, 16.0), 5: (32, 16.0), 64: (256, 4.0)}[bins]
+    g = gw.make_grid(N, -top, top, 0.05)
+    ctx = gw.Context(0)
+    dm = gw.DeviceMolecule(mol)
+    chi = torch.full((N, n, n), float("nan"), dtype=torch.complex128, device="cuda")
+    A = torch.full_like(chi, float("nan"))
+    ctx.build_chi0(dm.struct, g, chi)
+    ctx.build_A(dm.struct, dm.v, g, A)
+    ref = torch.eye(n, dtype=torch.complex128, device="cuda") - torch.stack([dm.v.to(torch.complex128) @ c for c in chi])
+    scale = float((dm.v.abs() @ chi.abs().amax(0)).amax()) + 1.0
+    assert float((A - ref).abs().amax()) <= 8 * (n + bins) * EPS * scale
+    ctx.close()
