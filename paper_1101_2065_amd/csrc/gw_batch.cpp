@@ -64,8 +64,10 @@ namespace {
 // rank-K trailing updates run on the split-BF16 kernel, and the FP32 table
 // entry serves its remaining complex-float products).  A class is measured the
 // first time it is seen, on the molecule's own first trailing update
-// (M = N = n - 256, K = 256, a batch of up to four frequencies): one warm-up
-// launch and five timed ones per tile, the median kept.  The table lives in
+// (M = N = n - 256, K = 256, as many frequencies as a factorisation batch holds
+// within 1 GiB: with four, a launch too small to fill the GPU made the smallest
+// tiles look best): one warm-up launch and five timed ones per tile, the median
+// kept.  The table lives in
 // memory and in a JSON file ($GW_TUNE_FILE, default $HOME/.cache/gw_tune.json).
 std::mutex g_tune_mu;
 std::map<std::string, int> g_tune;
@@ -96,13 +98,15 @@ gw_status tune_tile(gw_ctx *ctx, int n, gw_precision prec, hipStream_t st, int *
         return GW_OK;
     }
     const bool dbl = prec == GW_FP64;
-    const int M = n - 256, K = 256, batch = 4;
+    const int M = n - 256, K = 256;
     const size_t esz = dbl ? 16 : 8;
+    // as many frequencies as the factorisation's batches hold, within 1 GiB
+    const int batch = (int)std::max<size_t>(4, std::min<size_t>(256, ((size_t)1 << 30) / (((size_t)M * M + 2 * (size_t)M * K) * esz)));
     const size_t elems = (size_t)batch * ((size_t)M * M + 2 * (size_t)M * K);
     void *buf;
     gw_status s = gwp::ws(ctx, "tune", elems * esz, &buf);
     if (s != GW_OK) return s;
-    GW_HIP(ctx, gwk::launch_fill_u32(st, (uint32_t *)buf, (int64_t)(elems * esz / 4), 0u));
+    GW_HIP(ctx, gwk::launch_fill_test(st, (uint32_t *)buf, (int64_t)(elems * esz / 4), dbl));
     hipEvent_t e0, e1;
     GW_HIP(ctx, hipEventCreate(&e0));
     GW_HIP(ctx, hipEventCreate(&e1));

@@ -134,6 +134,9 @@ hipError_t launch_absmax(hipStream_t st, const double *P, int64_t n, uint64_t *d
 hipError_t launch_fracbits(hipStream_t st, const uint64_t *vmax_bits, int64_t n_pairs,
                            int requested, int32_t *s_out);
 
+// Test operands for timing: n 32-bit words of varied floats or doubles (equal or
+// zero operands draw less power, and products run faster on them).
+hipError_t launch_fill_test(hipStream_t st, uint32_t *p, int64_t n, bool dbl);
 hipError_t launch_fill_u64(hipStream_t st, uint64_t *p, int64_t n, uint64_t value);
 // A route: A[j] = 1 - (T X)[j] for all j from the products X = v a0 of the
 // bins ([nhb][n][n] real, xs values per bin; bin 0 is overwritten with the

@@ -1392,6 +1392,27 @@ hipError_t launch_transpose_d(hipStream_t st, int rows, int cols, const double *
     return hipGetLastError();
 }
 
+namespace {
+// Numbers of either sign in [1/2, 1): words (the high ones of doubles) of the
+// exponent and hashed bits.
+__global__ void k_fill_test(uint32_t *p, int64_t n, int dbl) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t h = (uint32_t)i * 2654435761u;
+        h = (h ^ (h >> 15)) * 2246822519u;
+        h ^= h >> 13;
+        if (!dbl) h = (h & 0x807fffffu) | 0x3f000000u;
+        else if (i & 1) h = (h & 0x800fffffu) | 0x3fe00000u;
+        p[i] = h;
+    }
+}
+}  // namespace
+
+hipError_t launch_fill_test(hipStream_t st, uint32_t *p, int64_t n, bool dbl) {
+    hipLaunchKernelGGL(k_fill_test, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 4096))),
+                       dim3(256), 0, st, p, n, dbl ? 1 : 0);
+    return hipGetLastError();
+}
+
 hipError_t launch_fill_u32(hipStream_t st, uint32_t *p, int64_t n, uint32_t value) {
     GW_DEFER(launch_fill_u32(st, p, n, value));
     int64_t blocks = (n + 255) / 256;
