@@ -1086,7 +1086,8 @@ static gw_status build_time_impl(gw_ctx *ctx, const gw_molecule *m, const double
     for (int q0 = 0; q0 < Q; q0 += qc) {
         const int nq = std::min(qc, Q - q0);
         GW_HIP(ctx, gwk::launch_time_contract(st, n_orb, n, class_off, q0, nq, m->blk_prod, m->blk_orb, m->orb_idx,
-                                              m->blk_val, m->vals, d_pb, d_pb + npb, Rp, Rm, Ahat, cflops * nq));
+                                              m->blk_val, m->vals, d_pb, d_pb + npb, Rp, Rm, Ahat, h.max_o,
+                                              cflops * nq));
         GW_HIP(ctx, gwk::launch_dgemm(st, nhb, (int)n_upper, 2 * nq, 1.0, G + 2 * q0, 2 * Q, 0, Ahat, n_upper, 0,
                                       q0 == 0 ? 0.0 : 1.0, a, n_upper, 0, 1));
     }

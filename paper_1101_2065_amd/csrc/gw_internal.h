@@ -289,7 +289,7 @@ hipError_t launch_dft_matrices(hipStream_t st, int L, int Q, int K, double *F, i
 hipError_t launch_time_contract(hipStream_t st, int n_orb, int n_prod, const int *class_off, int q0, int nq,
                                 const int32_t *blk_prod, const int32_t *blk_orb, const int32_t *orb_idx,
                                 const int64_t *blk_val, const double *vals, const int32_t *pb1, const int32_t *pb2,
-                                const double *Rp, const double *Rm, double *Ahat, double flops);
+                                const double *Rp, const double *Rm, double *Ahat, int max_orb, double flops);
 
 // ---------------------------------------------------------------- self-energy from W
 // gam[k][t] = -(domega/pi) Im W[j0 + k][mu][nu], packed upper t, k < n_sb; gam[0] = 0.
