@@ -1355,6 +1355,7 @@ int gemm_queue_occupancy(int key) {
     int occ = 0;
     hipError_t e = hipErrorInvalidValue;
     const int kind = key / 4, tile = key % 4;
+    if (kind == QK_SOLVE) return block_solve_occupancy(tile == 1);
 #define GW_QOCC(T, WM, WN, BK, OCC, M3) \
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gemm_queue<T, WM, WN, BK, OCC, M3>, 256, 0)
     GW_QKEY(GW_QOCC);
@@ -1362,6 +1363,11 @@ int gemm_queue_occupancy(int key) {
     return e == hipSuccess && occ > 0 ? occ : qshape(key).occ;
 }
 void gemm_queue_tile(int key, int *bm, int *bn) {
+    if (key / 4 == QK_SOLVE) {  // a strip of all the block's rows
+        *bm = 256;
+        *bn = 32;
+        return;
+    }
     const QShape q = qshape(key);
     *bm = 32 * q.wm;
     *bn = 32 * q.wn;
@@ -1370,10 +1376,11 @@ void gemm_queue_tile(int key, int *bm, int *bn) {
 hipError_t launch_gemm_queue(hipStream_t st, int key, const GemmItem *items, int n_items, int64_t n_tiles,
                              unsigned *queue, int grid, double flops) {
     if (n_items <= 0 || n_tiles <= 0) return hipSuccess;
-    if (key < 0 || key >= 12 || (!queue && n_tiles > INT32_MAX) || (queue && grid <= 0)) return hipErrorInvalidValue;
+    if (key < 0 || key >= 14 || (!queue && n_tiles > INT32_MAX) || (queue && grid <= 0)) return hipErrorInvalidValue;
     const int kind = key / 4, tile = key % 4;
-    static const char *const names[3] = {"zgemm3m_queue", "zgemm_queue", "cgemm_queue"};
+    static const char *const names[4] = {"zgemm3m_queue", "zgemm_queue", "cgemm_queue", "block_solve_queue"};
     ProfScope ps(st, names[kind], flops, 0.0);
+    if (kind == QK_SOLVE) return launch_block_solve_group(st, tile == 1, items, n_items, n_tiles);
 #define GW_QGEMM(T, WM, WN, BK, OCC, M3)                                                                       \
     do {                                                                                                       \
         if (queue)                                                                                             \
