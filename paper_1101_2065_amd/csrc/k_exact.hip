@@ -218,16 +218,23 @@ __global__ void k_fracbits(const uint64_t *vmax_bits, int64_t n_pairs, int reque
 // i.e. the lower share of bin m plus the upper share carried from bin m-1.
 // Integer additions are exact and associative, so the result does not depend
 // on the launch shape or the order of the pairs.
+//
+// Bound by the FP64 and 64-bit integer units: six instructions per pair and
+// entry.  So the pairs of a slice are staged in chunks that run on over the bin
+// boundaries, the next chunk's loads in flight in registers while this one is
+// multiplied (two workgroups per CU: for three the registers would spill).  2000
+// products, 57600 pairs, 512 bins: 27.8 ms with 16 slices (bin by bin, each
+// chunk's loads waited for one after another: 28.7; with 4 slices 32.9); 431
+// products, 2304 pairs: 0.116 ms (0.190).
 constexpr int HT = 64;  // tile edge
 constexpr int HC = 32;  // pairs per staged chunk
 
-__global__ __launch_bounds__(256) void k_hist(int n, int64_t ldp, const double *__restrict__ Ps,
-                                              const double *__restrict__ fsort,
-                                              const int32_t *__restrict__ binoff,
-                                              const int64_t *__restrict__ stat,
-                                              const int32_t *__restrict__ s_dev, int nhb,
-                                              unsigned long long *__restrict__ H, int64_t n_upper,
-                                              int ntiles, int splits, int bin_lo, int bin_hi) {
+__global__ __launch_bounds__(256, 2) void k_hist(int n, int64_t ldp, const double *__restrict__ Ps,
+                                                 const double *__restrict__ fsort,
+                                                 const int32_t *__restrict__ binoff,
+                                                 const int32_t *__restrict__ s_dev, int nhb,
+                                                 unsigned long long *__restrict__ H, int64_t n_upper,
+                                                 int ntiles, int splits, int bin_lo, int bin_hi) {
 #pragma clang fp contract(off)
     // rows padded by one value: the staging stores walk down a column
     __shared__ double Pm[HC][HT + 1];
@@ -243,7 +250,6 @@ __global__ __launch_bounds__(256) void k_hist(int n, int64_t ldp, const double *
     const int tj = ti + t;
     const int mu0 = ti * HT, nu0 = tj * HT;
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    (void)stat;  // the kept-pair count is binoff[nhb - 1]
     const int s = *s_dev;
     const double twos = ldexp(1.0, s);
     // bin slice [mb, me) of this split: only pairs whose lower bin lies in
@@ -268,45 +274,83 @@ __global__ __launch_bounds__(256) void k_hist(int n, int64_t ldp, const double *
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) A[i][j] = B[i][j] = Bp[i][j] = 0;
-    bool valid[4][4];
-    int64_t tidx[4][4];
+    // value k of a thread in a chunk: row sr + 8 k of the tile, pair sc
+    const int sc = threadIdx.x % HC, sr = threadIdx.x / HC;
+    const int p_begin = binoff[mb], p_end = binoff[me];
+    double ga[HT / 8], gb[HT / 8], gw = 0.0;
+    auto fetch = [&](int c0) {
+        int64_t ld = ldp;
+        asm volatile("" : "+s"(ld));  // no row address is held in registers from chunk to chunk
+        const int64_t p = min(c0 + sc, p_end - 1);  // (past the end: a copy that no loop reaches)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int mu = mu0 + ty + 16 * i, nu = nu0 + tx + 16 * j;
-            valid[i][j] = (mu < n) && (nu < n) && (mu <= nu);
-            tidx[i][j] = (int64_t)mu * n - ((int64_t)mu * (mu - 1)) / 2 + (nu - mu);
+        for (int k = 0; k < HT / 8; ++k) {
+            ga[k] = Ps[min(mu0 + sr + 8 * k, n - 1) * ld + p];
+            gb[k] = Ps[min(nu0 + sr + 8 * k, n - 1) * ld + p];
         }
-
-    for (int m = mb; m < me; ++m) {
-        const int64_t p0 = binoff[m], p1 = binoff[m + 1];
-        for (int64_t c0 = p0; c0 < p1; c0 += HC) {
-            const int cnt = (int)min((int64_t)HC, p1 - c0);
-            __syncthreads();
-            for (int r = threadIdx.x; r < HC * HT; r += 256) {
-                const int row = r / HC, col = r % HC;
-                double a = 0.0, b = 0.0;
-                if (col < cnt) {
-                    if (mu0 + row < n) a = Ps[(int64_t)(mu0 + row) * ldp + c0 + col];
-                    if (nu0 + row < n) b = Ps[(int64_t)(nu0 + row) * ldp + c0 + col];
+        if (threadIdx.x < HC) gw = fsort[p];
+    };
+    // this thread's entry (i, j) of a row at Hm, null outside the triangle
+    auto entry = [&](unsigned long long *Hm, int i, int j) -> unsigned long long * {
+        int mu = ty + 16 * i;
+        asm volatile("" : "+v"(mu));  // nor any entry's index from bin to bin
+        mu += mu0;
+        const int nu = nu0 + tx + 16 * j;
+        if (nu >= n || mu > nu) return nullptr;
+        return Hm + ((int64_t)mu * n - ((int64_t)mu * (mu - 1)) / 2 + (nu - mu));
+    };
+    auto flush = [&](int m, int count) {
+        const uint64_t off = (uint64_t)count * kMagicBits;
+        unsigned long long *Hm = H + (int64_t)m * n_upper;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint64_t val = 2ull * (A[i][j] - B[i][j] + Bp[i][j]);
+                unsigned long long *h = entry(Hm, i, j);
+                if (h && val != 0ull) {
+                    // the slice's first bin also takes the upper share of the
+                    // slice before it; the others are this workgroup's alone
+                    if (m == mb) atomicAdd(h, (unsigned long long)val);
+                    else *h = val;
                 }
-                Pm[col][row] = a;
-                Pn[col][row] = b;
+                Bp[i][j] = B[i][j] - off;
+                A[i][j] = 0;
+                B[i][j] = 0;
             }
-            if (threadIdx.x < HC) wv[threadIdx.x] = threadIdx.x < cnt ? ldexp(fsort[c0 + threadIdx.x], s) : 0.0;
-            __syncthreads();
-            for (int pp = 0; pp < cnt; ++pp) {
-                const double w = wv[pp];
+    };
+    int m = mb, m_begin = p_begin, m_end = binoff[mb + 1];
+    if (p_begin < p_end) fetch(p_begin);
+    for (int c0 = p_begin; c0 < p_end; c0 += HC) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < HT / 8; ++k) {
+            Pm[sc][sr + 8 * k] = ga[k];
+            Pn[sc][sr + 8 * k] = gb[k];
+        }
+        if (threadIdx.x < HC) wv[threadIdx.x] = ldexp(gw, s);
+        __syncthreads();
+        if (c0 + HC < p_end) fetch(c0 + HC);
+        const int c1 = min(c0 + HC, p_end);
+        int p = c0;
+        while (p < c1) {
+            while (p == m_end) {
+                flush(m, m_end - m_begin);
+                ++m;
+                m_begin = m_end;
+                m_end = binoff[m + 1];
+            }
+            const int pe = min(m_end, c1);
+            for (; p < pe; ++p) {
+                const double w = wv[p - c0];
                 double u[4], y[4], vn[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const double vm = Pm[pp][ty + 16 * i];
+                    const double vm = Pm[p - c0][ty + 16 * i];
                     u[i] = __dmul_rn(vm, twos);
                     y[i] = __dmul_rn(vm, w);
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) vn[j] = Pn[pp][tx + 16 * j];
+                for (int j = 0; j < 4; ++j) vn[j] = Pn[p - c0][tx + 16 * j];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -318,25 +362,19 @@ __global__ __launch_bounds__(256) void k_hist(int n, int64_t ldp, const double *
                     }
             }
         }
-        const uint64_t off = (uint64_t)(p1 - p0) * kMagicBits;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint64_t val = 2ull * (A[i][j] - B[i][j] + Bp[i][j]);
-                if (valid[i][j] && val != 0ull)
-                    atomicAdd(&H[(int64_t)m * n_upper + tidx[i][j]], (unsigned long long)val);
-                Bp[i][j] = B[i][j] - off;
-                A[i][j] = 0;
-                B[i][j] = 0;
-            }
+    }
+    for (; m < me; ++m) {
+        flush(m, m_end - m_begin);
+        m_begin = m_end;
+        if (m + 1 < me) m_end = binoff[m + 2];
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint64_t val = 2ull * Bp[i][j];
-            if (valid[i][j] && val != 0ull) atomicAdd(&H[(int64_t)me * n_upper + tidx[i][j]], (unsigned long long)val);
+            unsigned long long *h = entry(H + (int64_t)me * n_upper, i, j);
+            if (h && val != 0ull) atomicAdd(h, (unsigned long long)val);
         }
 }
 
@@ -426,7 +464,7 @@ hipError_t launch_hist(hipStream_t st, int n, int64_t n_pairs_cap, const double 
     if (splits < 1) splits = 1;
     ProfScope ps(st, "hist", (double)n_pairs_cap * n_upper,
                  8.0 * (double)n_pairs_cap * n + 8.0 * (bin_hi - bin_lo + 1) * n_upper);
-    hipLaunchKernelGGL(k_hist, dim3(ntp, splits), dim3(256), 0, st, n, n_pairs_cap, Ps, fsort, binoff, stat, s_dev,
+    hipLaunchKernelGGL(k_hist, dim3(ntp, splits), dim3(256), 0, st, n, n_pairs_cap, Ps, fsort, binoff, s_dev,
                        nhb, (unsigned long long *)H, n_upper, ntiles, splits, bin_lo, bin_hi);
     return hipGetLastError();
 }
