@@ -91,15 +91,18 @@ using dglobal = P;
         }                                                               \
     } while (0)
 // product kinds of the work-queue launch; QK_SOLVE: substitution inside a block
-// (k_trsm.hip; tile 0 lower, 1 upper), a GemmItem with A = the triangle, B = its
+// (k_trsm.hip; tile 0 lower, 1 upper, + 2 complex float), a GemmItem with A = the triangle, B = its
 // inverted diagonal blocks, C = the right-hand sides, M x N theirs, K = tri
 enum { QK_Z3M = 0, QK_Z4M = 1, QK_C = 2, QK_SOLVE = 3 };
 // X <- L^{-1} X or U^{-1} X for one block (wo <= 256) of a factorisation; tri
 // >= 0: only the lower triangle of a symmetric result is needed (see k_trsm.hip).
 hipError_t launch_block_solve(hipStream_t st, bool upper, int wo, int n, const zdbl *T, int64_t ldt, int64_t sT,
                               const zdbl *inv, int64_t sI, zdbl *X, int64_t ldx, int64_t sX, int batch, int tri);
-hipError_t launch_block_solve_group(hipStream_t st, bool upper, const GemmItem *items, int n_items, int64_t n_tiles);
-int block_solve_occupancy(bool upper);
+hipError_t launch_block_solve(hipStream_t st, bool upper, int wo, int n, const zflt *T, int64_t ldt, int64_t sT,
+                              const zflt *inv, int64_t sI, zflt *X, int64_t ldx, int64_t sX, int batch, int tri);
+hipError_t launch_block_solve_group(hipStream_t st, int variant, const GemmItem *items, int n_items, int64_t n_tiles);
+int block_solve_occupancy(int variant);
+int block_solve_columns(int variant);  // columns of a strip
 // One launch of `n_items` products (descriptors on the device), `n_tiles`
 // tiles in all: with `queue` (eight counters, zero) a persistent grid of
 // `grid` workgroups pulling tiles from per-XCD work queues, without it one

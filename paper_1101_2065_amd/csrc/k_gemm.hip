@@ -1231,7 +1231,7 @@ hipError_t launch_zdgemm_wide(hipStream_t st, int M, int N, int K, double alpha,
 }
 
 // Complex-float products of the calling thread run as split-BF16 MFMA when set
-// (the trailing updates of the BF16x LU).
+// (the long products of the BF16x factorisation and solves).
 thread_local bool g_cgemm_bf16x = false;
 
 hipError_t launch_cgemm(hipStream_t st, int M, int N, int K, float alpha, const zflt *A, int64_t lda, int64_t sA,
@@ -1355,7 +1355,7 @@ int gemm_queue_occupancy(int key) {
     int occ = 0;
     hipError_t e = hipErrorInvalidValue;
     const int kind = key / 4, tile = key % 4;
-    if (kind == QK_SOLVE) return block_solve_occupancy(tile == 1);
+    if (kind == QK_SOLVE) return block_solve_occupancy(tile);
 #define GW_QOCC(T, WM, WN, BK, OCC, M3) \
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gemm_queue<T, WM, WN, BK, OCC, M3>, 256, 0)
     GW_QKEY(GW_QOCC);
@@ -1365,7 +1365,7 @@ int gemm_queue_occupancy(int key) {
 void gemm_queue_tile(int key, int *bm, int *bn) {
     if (key / 4 == QK_SOLVE) {  // a strip of all the block's rows
         *bm = 256;
-        *bn = 32;
+        *bn = block_solve_columns(key % 4);
         return;
     }
     const QShape q = qshape(key);
@@ -1376,11 +1376,11 @@ void gemm_queue_tile(int key, int *bm, int *bn) {
 hipError_t launch_gemm_queue(hipStream_t st, int key, const GemmItem *items, int n_items, int64_t n_tiles,
                              unsigned *queue, int grid, double flops) {
     if (n_items <= 0 || n_tiles <= 0) return hipSuccess;
-    if (key < 0 || key >= 14 || (!queue && n_tiles > INT32_MAX) || (queue && grid <= 0)) return hipErrorInvalidValue;
+    if (key < 0 || key >= 16 || (!queue && n_tiles > INT32_MAX) || (queue && grid <= 0)) return hipErrorInvalidValue;
     const int kind = key / 4, tile = key % 4;
     static const char *const names[4] = {"zgemm3m_queue", "zgemm_queue", "cgemm_queue", "block_solve_queue"};
     ProfScope ps(st, names[kind], flops, 0.0);
-    if (kind == QK_SOLVE) return launch_block_solve_group(st, tile == 1, items, n_items, n_tiles);
+    if (kind == QK_SOLVE) return launch_block_solve_group(st, tile, items, n_items, n_tiles);
 #define GW_QGEMM(T, WM, WN, BK, OCC, M3)                                                                       \
     do {                                                                                                       \
         if (queue)                                                                                             \

@@ -1025,34 +1025,17 @@ hipError_t gemm_t<float>(hipStream_t st, int M, int N, int K, float alpha, const
                         sC, batch);
 }
 
-// Substitution inside one outer block: X <- T^{-1} X for its triangle T (wo x
-// wo), whose diagonal blocks come inverted; with tri >= 0 (upper) panel p of X
-// is needed in columns below tri + 64 (p + 1) alone.  Complex double in one
-// launch (k_trsm.hip); complex float panel by panel, a product for the panel
-// and one for the block's rows that wait for it.
-template <typename T>
-hipError_t block_solve_t(hipStream_t st, bool upper, int wo, int n, const Cx<T> *Tm, int64_t ldt, int64_t sT,
-                         const Cx<T> *inv, int64_t sI, Cx<T> *X, int64_t ldx, int64_t sX, int batch, int tri) {
-    if constexpr (sizeof(T) == 8) {
-        return launch_block_solve(st, upper, wo, n, (const zdbl *)Tm, ldt, sT, (const zdbl *)inv, sI, (zdbl *)X, ldx,
-                                  sX, batch, tri);
-    } else {
-        const int np = (wo + NB - 1) / NB;
-        for (int s = 0; s < np; ++s) {
-            const int p = upper ? np - 1 - s : s, k = p * NB, w = min(NB, wo - k);
-            Cx<T> *Xk = X + (int64_t)k * ldx;
-            hipError_t e = gemm_t<T>(st, w, tri >= 0 ? tri + k + w : n, w, T(1), inv + (int64_t)p * NB * NB, NB, sI, Xk,
-                                     ldx, sX, T(0), Xk, ldx, sX, batch);
-            if (e != hipSuccess) return e;
-            // the rows still to come: above the panel (upper) or below it
-            const int r = upper ? 0 : k + w, rows = upper ? k : wo - k - w;
-            if (rows == 0) continue;
-            e = gemm_t<T>(st, rows, tri >= 0 ? tri + k : n, w, T(-1), Tm + (int64_t)r * ldt + k, ldt, sT, Xk, ldx, sX,
-                          T(1), X + (int64_t)r * ldx, ldx, sX, batch);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
-    }
+inline hipError_t block_solve_t(hipStream_t st, bool upper, int wo, int n, const Cx<double> *Tm, int64_t ldt, int64_t sT,
+                                const Cx<double> *inv, int64_t sI, Cx<double> *X, int64_t ldx, int64_t sX, int batch,
+                                int tri) {
+    return launch_block_solve(st, upper, wo, n, (const zdbl *)Tm, ldt, sT, (const zdbl *)inv, sI, (zdbl *)X, ldx, sX,
+                              batch, tri);
+}
+inline hipError_t block_solve_t(hipStream_t st, bool upper, int wo, int n, const Cx<float> *Tm, int64_t ldt, int64_t sT,
+                                const Cx<float> *inv, int64_t sI, Cx<float> *X, int64_t ldx, int64_t sX, int batch,
+                                int tri) {
+    return launch_block_solve(st, upper, wo, n, (const zflt *)Tm, ldt, sT, (const zflt *)inv, sI, (zflt *)X, ldx, sX,
+                              batch, tri);
 }
 
 // Two-level blocking: 64-wide panels inside 256-wide blocks.  Inside a block
@@ -1148,7 +1131,7 @@ hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv
         const int rest = n - KB - WO;
         if (rest > 0) {
             // U12 rows of the block
-            e = block_solve_t<T>(st, false, WO, rest, A + (int64_t)KB * n + KB, n, sA,
+            e = block_solve_t(st, false, WO, rest, A + (int64_t)KB * n + KB, n, sA,
                                  Linv + (int64_t)(KB / NB) * NB * NB, sI, A + (int64_t)KB * n + KB + WO, n, sA, batch,
                                  -1);
             if (e != hipSuccess) return e;
@@ -1207,7 +1190,7 @@ hipError_t getrs_impl(hipStream_t st, int n, int nrhs, const Cx<T> *LU, int64_t 
                           B + (int64_t)KB * nrhs, nrhs, sB, batch);
             if (e != hipSuccess) return e;
         }
-        e = block_solve_t<T>(st, false, WO, nrhs, LU + (int64_t)KB * n + KB, n, sA,
+        e = block_solve_t(st, false, WO, nrhs, LU + (int64_t)KB * n + KB, n, sA,
                              Linv + (int64_t)(KB / NB) * NB * NB, sI, B + (int64_t)KB * nrhs, nrhs, sB, batch, -1);
         if (e != hipSuccess) return e;
     }
@@ -1223,7 +1206,7 @@ hipError_t getrs_impl(hipStream_t st, int n, int nrhs, const Cx<T> *LU, int64_t 
                           B + (int64_t)(KB + WO) * nrhs, nrhs, sB, T(1), B + (int64_t)KB * nrhs, nrhs, sB, batch);
             if (e != hipSuccess) return e;
         }
-        e = block_solve_t<T>(st, true, WO, sym_lower ? KB + WO : nrhs, LU + (int64_t)KB * n + KB, n, sA,
+        e = block_solve_t(st, true, WO, sym_lower ? KB + WO : nrhs, LU + (int64_t)KB * n + KB, n, sA,
                              Uinv + (int64_t)(KB / NB) * NB * NB, sI, B + (int64_t)KB * nrhs, nrhs, sB, batch,
                              sym_lower ? KB : -1);
         if (e != hipSuccess) return e;

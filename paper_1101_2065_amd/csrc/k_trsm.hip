@@ -1,12 +1,12 @@
 // Substitution inside a 256-row block of the blocked LU and solves (complex
-// FP64): X <- L^{-1} X or U^{-1} X for the block's triangle, whose 64 x 64
+// FP64 and FP32): X <- L^{-1} X or U^{-1} X for the block's triangle, whose 64 x 64
 // diagonal blocks come inverted (Section 2 eq. Coulombscreening, the dense
 // solve of W).
 //
 // Panel by panel, X_p <- T_pp^{-1} X_p, then X_q -= T_qp X_p for the panels q
 // still to come.  As separate products these were bound by HBM: each K = 64
 // update reads and writes all the rows below it (44-55 TF in 8MNK).  Here a
-// workgroup keeps a strip of 32 columns of all 256 rows in registers, so X is
+// workgroup keeps a strip of 32 columns (FP32: 64) of all 256 rows in registers, so X is
 // read and written once and the products run from LDS: wave w holds rows
 // 16 w .. 16 w + 15 of every panel, which gives the four waves equal shares of
 // every step.  X_p goes through LDS as the matrix-core operand B (the register
@@ -16,8 +16,10 @@
 // 256 rows, 2000 columns, 120 matrices: 1.07 ms, 74 TF in 8MNK (62 TF for 8
 // matrices, whose 504 strips just fill the chip); bound by the matrix cores (103
 // TF in this count) and, at two waves per SIMD, the latency around the barriers
-// of its ten steps.  A launch for seven: 39 solves of n = 1100 take 25 ms instead
-// of 38.  Strips of 32 columns: 64 would leave one wave per SIMD (registers).
+// of its ten steps.  n = 1100: 25 ms of launches where the products took 32.
+// Wider strips would leave one wave per SIMD (registers).  FP32, 517 and 655
+// rows, 128 frequencies, three solves: 4.2 ms of launches for 6.5 of FP32
+// products, 5.8 for 7.2 of split-BF16 ones.
 #include "gw_internal.h"
 #include "gw_prof.h"
 #include "k_mfma.h"
@@ -30,39 +32,73 @@ namespace {
 
 constexpr int TNB = 64;  // panel
 
-typedef double td2 __attribute__((ext_vector_type(2)));
-typedef double td2u __attribute__((ext_vector_type(2), aligned(8)));
-typedef Mfma<double>::v4 tv4;
-
-// acc += A B over 64 k for this wave's 16 rows and 32 columns, as three real
-// products (ac, bd, (a + b)(c + d)); ap: the lane's value of A at k = lane / 16,
-// already holding the first four steps in a; kmax: the last k with data.
-struct Acc {
-    tv4 r[2], i[2], s[2];
+template <typename T>
+struct Tv;
+template <>
+struct Tv<double> {
+    typedef double v2 __attribute__((ext_vector_type(2)));
+    typedef double v2u __attribute__((ext_vector_type(2), aligned(8)));
+    static constexpr int NH = 2;  // sixteens of columns in a strip
 };
-template <typename G2>
-__device__ __forceinline__ void load4(td2 (&a)[4], const G2 *row, int k0, int lk, int kmax) {
+template <>
+struct Tv<float> {
+    typedef float v2 __attribute__((ext_vector_type(2)));
+    typedef float v2u __attribute__((ext_vector_type(2), aligned(4)));
+    static constexpr int NH = 4;
+};
+
+// c = A B over 64 k for this wave's 16 rows and the strip's columns: FP64 as
+// three real products (ac, bd, (a + b)(c + d)), FP32 as four.  row: the lane's
+// row of A; a already holds its first four steps (k = lane / 16 + 4 q).
+template <typename T>
+struct Acc {
+    typedef typename Mfma<T>::v4 v4;
+    static constexpr bool M3 = sizeof(T) == 8;
+    v4 r[Tv<T>::NH], i[Tv<T>::NH], s[M3 ? Tv<T>::NH : 1];
+    __device__ __forceinline__ T re(int h, int e) const { return M3 ? r[h][e] - i[h][e] : r[h][e]; }
+    __device__ __forceinline__ T im(int h, int e) const {
+        return M3 ? s[M3 ? h : 0][e] - r[h][e] - i[h][e] : i[h][e];
+    }
+};
+template <typename V2, typename G2>
+__device__ __forceinline__ void load4(V2 (&a)[4], const G2 *row, int k0, int lk, int kmax) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) a[q] = row[min(k0 + 4 * q + lk, kmax)];
 }
-template <typename G2>
-__device__ __forceinline__ void mul64(Acc &c, td2 (&a)[4], const G2 *row, int lk, int lane, int kmax, const td2 *b) {
+template <typename T, typename G2, typename V2>
+__device__ __forceinline__ void mul64(Acc<T> &c, V2 (&a)[4], const G2 *row, int lk, int lane, int kmax, const V2 *b) {
+    typedef typename Mfma<T>::v4 v4;
+    constexpr int NH = Tv<T>::NH;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) c.r[j] = c.i[j] = c.s[j] = tv4{0, 0, 0, 0};
+    for (int j = 0; j < NH; ++j) {
+        c.r[j] = c.i[j] = v4{0, 0, 0, 0};
+        if constexpr (Acc<T>::M3) c.s[j] = v4{0, 0, 0, 0};
+    }
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
-        td2 n[4];
+        V2 n[4];
         if (h < 3) load4(n, row, 16 * (h + 1), lk, kmax);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const td2 b0 = b[(2 * (4 * h + q)) * 64 + lane], b1 = b[(2 * (4 * h + q) + 1) * 64 + lane];
-            const double sa = a[q].x + a[q].y, s0 = b0.x + b0.y, s1 = b1.x + b1.y;
-            c.r[0] = Mfma<double>::op(a[q].x, b0.x, c.r[0]);
-            c.r[1] = Mfma<double>::op(a[q].x, b1.x, c.r[1]);
-            c.i[0] = Mfma<double>::op(a[q].y, b0.y, c.i[0]);
-            c.i[1] = Mfma<double>::op(a[q].y, b1.y, c.i[1]);
-            c.s[0] = Mfma<double>::op(sa, s0, c.s[0]);
-            c.s[1] = Mfma<double>::op(sa, s1, c.s[1]);
+            V2 bv[NH];
+#pragma unroll
+            for (int j = 0; j < NH; ++j) bv[j] = b[(NH * (4 * h + q) + j) * 64 + lane];
+#pragma unroll
+            for (int j = 0; j < NH; ++j) c.r[j] = Mfma<T>::op(a[q].x, bv[j].x, c.r[j]);
+            if constexpr (Acc<T>::M3) {
+                const T sa = a[q].x + a[q].y;
+#pragma unroll
+                for (int j = 0; j < NH; ++j) c.i[j] = Mfma<T>::op(a[q].y, bv[j].y, c.i[j]);
+#pragma unroll
+                for (int j = 0; j < NH; ++j) c.s[j] = Mfma<T>::op(sa, bv[j].x + bv[j].y, c.s[j]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NH; ++j) c.i[j] = Mfma<T>::op(a[q].x, bv[j].y, c.i[j]);
+#pragma unroll
+                for (int j = 0; j < NH; ++j) c.r[j] = Mfma<T>::op(-a[q].y, bv[j].y, c.r[j]);
+#pragma unroll
+                for (int j = 0; j < NH; ++j) c.i[j] = Mfma<T>::op(a[q].y, bv[j].x, c.i[j]);
+            }
         }
         if (h < 3) {
 #pragma unroll
@@ -77,24 +113,31 @@ __device__ __forceinline__ void mul64(Acc &c, td2 (&a)[4], const G2 *row, int lk
 // (upper only): the block's first row's index among X's columns; panel p is
 // then needed in columns below tri + 64 (p + 1) alone (a symmetric result, its
 // lower triangle).
-template <bool UPPER, typename G2>
-__device__ __forceinline__ void solve_strip(int wo, int n, const G2 *T, int64_t ldt, const G2 *inv, G2 *X, int64_t ldx,
+template <typename T, bool UPPER, typename G2>
+__device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t ldt, const G2 *inv, G2 *X, int64_t ldx,
                                             int tri, int c0) {
-    __shared__ td2 xb[32 * 64], yb[32 * 64];  // X_p before and after its diagonal block
+    typedef typename Tv<T>::v2 V2;
+    constexpr int NH = Tv<T>::NH;
+    __shared__ V2 xb[NH * TNB * 16], yb[NH * TNB * 16];  // X_p before and after its diagonal block
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = lane & 15, lk = lane >> 4;
     const int np = (wo + TNB - 1) / TNB;
+    // where a result's row goes as operand B: step k / 4, lanes 16 (k % 4) ..
+    auto slot = [&](int h, int e) {
+        const int k = Mfma<T>::row(lane, e);
+        return (NH * (4 * wave + (k >> 2)) + h) * 64 + 16 * (k & 3) + lr;
+    };
     // panels in order of solution: step s is panel s, or np - 1 - s
     const int first = tri >= 0 ? max(0, (c0 - tri) / TNB) : 0;  // upper: panels below it are not needed
-    td2 x[4][2][4];  // [panel][column half][e]: row 64 p + 16 wave + lk + 4 e, column c0 + 16 h + lr
+    V2 x[4][NH][4];  // [panel][sixteen of columns][e]: row 64 p + 16 wave + Mfma row e, column c0 + 16 h + lr
 #pragma unroll
     for (int p = 0; p < 4; ++p)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int row = TNB * p + 16 * wave + lk + 4 * e, col = c0 + 16 * h + lr;
-                x[p][h][e] = td2{0, 0};
+                const int row = TNB * p + 16 * wave + Mfma<T>::row(lane, e), col = c0 + 16 * h + lr;
+                x[p][h][e] = V2{0, 0};
                 if (p >= first && row < wo && col < n) x[p][h][e] = X[(int64_t)row * ldx + col];
             }
 #pragma unroll
@@ -105,28 +148,28 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *T, int64_t 
         const int p = UPPER ? last - s : s;
         if (p >= np || p < first) continue;  // uniform
         const G2 *di = inv + (int64_t)p * TNB * TNB + (16 * wave + lr) * TNB;
-        td2 a[4];
+        V2 a[4];
         load4(a, di, 0, lk, TNB - 1);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) xb[(2 * (4 * wave + e) + h) * 64 + lane] = x[p][h][e];
+            for (int e = 0; e < 4; ++e) xb[slot(h, e)] = x[p][h][e];
         __syncthreads();
-        Acc c;
-        mul64(c, a, di, lk, lane, TNB - 1, xb);
+        Acc<T> c;
+        mul64<T>(c, a, di, lk, lane, TNB - 1, xb);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const td2 y{c.r[h][e] - c.i[h][e], c.s[h][e] - c.r[h][e] - c.i[h][e]};
-                yb[(2 * (4 * wave + e) + h) * 64 + lane] = y;
-                const int row = TNB * p + 16 * wave + lk + 4 * e, col = c0 + 16 * h + lr;
+                const V2 y{c.re(h, e), c.im(h, e)};
+                yb[slot(h, e)] = y;
+                const int row = TNB * p + 16 * wave + Mfma<T>::row(lane, e), col = c0 + 16 * h + lr;
                 if (row < wo && col < n) X[(int64_t)row * ldx + col] = y;
             }
         // the panels still to come
         const int kmax = min(TNB, wo - TNB * p) - 1;
         auto row_of = [&](int q) {
-            return T + (int64_t)min(TNB * q + 16 * wave + lr, wo - 1) * ldt + TNB * p;
+            return Tm + (int64_t)min(TNB * q + 16 * wave + lr, wo - 1) * ldt + TNB * p;
         };
         bool have = false;
 #pragma unroll
@@ -138,13 +181,13 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *T, int64_t 
             load4(a, row, 0, lk, kmax);
             if (!have) __syncthreads();  // yb is complete
             have = true;
-            mul64(c, a, row, lk, lane, kmax, yb);
+            mul64<T>(c, a, row, lk, lane, kmax, yb);
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < NH; ++h)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    x[q][h][e].x = -(c.r[h][e] - c.i[h][e]) + x[q][h][e].x;
-                    x[q][h][e].y = -(c.s[h][e] - c.r[h][e] - c.i[h][e]) + x[q][h][e].y;
+                    x[q][h][e].x = -c.re(h, e) + x[q][h][e].x;
+                    x[q][h][e].y = -c.im(h, e) + x[q][h][e].y;
                 }
         }
         // (no reader of xb or yb is left behind: the next step writes xb after
@@ -152,24 +195,24 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *T, int64_t 
     }
 }
 
-template <bool UPPER>
-__global__ __launch_bounds__(256, 2) void k_block_solve(int wo, int n, const double *T_, int64_t ldt, int64_t sT,
-                                                        const double *inv_, int64_t sI, double *X_, int64_t ldx,
+template <typename T, bool UPPER>
+__global__ __launch_bounds__(256, 2) void k_block_solve(int wo, int n, const T *T_, int64_t ldt, int64_t sT,
+                                                        const T *inv_, int64_t sI, T *X_, int64_t ldx,
                                                         int64_t sX, int tri) {
-    typedef dglobal<td2u> G2;
+    typedef dglobal<typename Tv<T>::v2u> G2;
     const int64_t nt = (int64_t)gridDim.x * gridDim.y, l = blockIdx.x + (int64_t)gridDim.x * blockIdx.y;
     const int64_t n8 = nt / 8, t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;  // one matrix's strips on one XCD
     const int64_t b = t / gridDim.x;
-    solve_strip<UPPER, G2>(wo, n, (const G2 *)T_ + b * sT, ldt, (const G2 *)inv_ + b * sI, (G2 *)X_ + b * sX, ldx, tri,
-                           (int)(t % gridDim.x) * 32);
+    solve_strip<T, UPPER, G2>(wo, n, (const G2 *)T_ + b * sT, ldt, (const G2 *)inv_ + b * sI, (G2 *)X_ + b * sX, ldx,
+                              tri, (int)(t % gridDim.x) * 16 * Tv<T>::NH);
 }
 
 // Many batched block solves in one launch, a strip per workgroup, in the order
 // of k_block_solve.
-template <bool UPPER>
+template <typename T, bool UPPER>
 __global__ __launch_bounds__(256, 2) void k_block_solve_group(const GemmItem *__restrict__ items, int n_items,
                                                               int64_t n_tiles) {
-    typedef dglobal<td2u> G2;
+    typedef dglobal<typename Tv<T>::v2u> G2;
     const int64_t l = blockIdx.x, n8 = n_tiles / 8;
     const int64_t t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;
     int a = 0, b = n_items - 1;
@@ -180,14 +223,13 @@ __global__ __launch_bounds__(256, 2) void k_block_solve_group(const GemmItem *__
     }
     const GemmItem g = items[a];
     const int64_t r = t - g.t0, bz = r / g.tx;
-    solve_strip<UPPER, G2>(g.M, g.N, (const G2 *)g.A + bz * g.sA, g.lda, (const G2 *)g.B + bz * g.sB,
-                           (G2 *)g.C + bz * g.sC, g.ldc, g.K, (int)(r - bz * g.tx) * 32);
+    solve_strip<T, UPPER, G2>(g.M, g.N, (const G2 *)g.A + bz * g.sA, g.lda, (const G2 *)g.B + bz * g.sB,
+                              (G2 *)g.C + bz * g.sC, g.ldc, g.K, (int)(r - bz * g.tx) * 16 * Tv<T>::NH);
 }
 
-}  // namespace
-
-hipError_t launch_block_solve(hipStream_t st, bool upper, int wo, int n, const zdbl *T, int64_t ldt, int64_t sT,
-                              const zdbl *inv, int64_t sI, zdbl *X, int64_t ldx, int64_t sX, int batch, int tri) {
+template <typename T, typename Z>
+hipError_t block_solve(hipStream_t st, bool upper, int wo, int n, const Z *Tm, int64_t ldt, int64_t sT, const Z *inv,
+                       int64_t sI, Z *X, int64_t ldx, int64_t sX, int batch, int tri) {
     if (wo <= 0 || n <= 0 || batch <= 0) return hipSuccess;
     if (wo > 4 * TNB || batch > 65535) return hipErrorInvalidValue;
     if (!upper) tri = -1;
@@ -196,36 +238,59 @@ hipError_t launch_block_solve(hipStream_t st, bool upper, int wo, int n, const z
     if (OpRecorder *rec = g_rec) {
         RecOp o;
         o.kind = RecOp::GEMM;
-        o.key = QK_SOLVE * 4 + (upper ? 1 : 0);
-        o.g = GemmItem{T, inv, X, ldt, 0, ldx, sT, sI, sX, 0.0, 0.0, wo, n, tri, batch, 0, 0, 0};
+        o.key = QK_SOLVE * 4 + (sizeof(T) == 4 ? 2 : 0) + (upper ? 1 : 0);
+        o.g = GemmItem{Tm, inv, X, ldt, 0, ldx, sT, sI, sX, 0.0, 0.0, wo, n, tri, batch, 0, 0, 0};
         o.flops = flops;
         rec->ops.push_back(std::move(o));
         return hipSuccess;
     }
-    ProfScope ps(st, "block_solve", flops, 32.0 * wo * (double)n * batch);
-    const dim3 grid((unsigned)((n + 31) / 32), (unsigned)batch);
+    ProfScope ps(st, sizeof(T) == 4 ? "block_solve_c" : "block_solve", flops, 4.0 * sizeof(T) * wo * (double)n * batch);
+    const int cols = 16 * Tv<T>::NH;
+    const dim3 grid((unsigned)((n + cols - 1) / cols), (unsigned)batch);
     if (upper)
-        hipLaunchKernelGGL((k_block_solve<true>), grid, dim3(256), 0, st, wo, n, (const double *)T, ldt, sT,
-                           (const double *)inv, sI, (double *)X, ldx, sX, tri);
+        hipLaunchKernelGGL((k_block_solve<T, true>), grid, dim3(256), 0, st, wo, n, (const T *)Tm, ldt, sT,
+                           (const T *)inv, sI, (T *)X, ldx, sX, tri);
     else
-        hipLaunchKernelGGL((k_block_solve<false>), grid, dim3(256), 0, st, wo, n, (const double *)T, ldt, sT,
-                           (const double *)inv, sI, (double *)X, ldx, sX, tri);
+        hipLaunchKernelGGL((k_block_solve<T, false>), grid, dim3(256), 0, st, wo, n, (const T *)Tm, ldt, sT,
+                           (const T *)inv, sI, (T *)X, ldx, sX, tri);
     return hipGetLastError();
 }
 
-hipError_t launch_block_solve_group(hipStream_t st, bool upper, const GemmItem *items, int n_items, int64_t n_tiles) {
+}  // namespace
+
+hipError_t launch_block_solve(hipStream_t st, bool upper, int wo, int n, const zdbl *T, int64_t ldt, int64_t sT,
+                              const zdbl *inv, int64_t sI, zdbl *X, int64_t ldx, int64_t sX, int batch, int tri) {
+    return block_solve<double>(st, upper, wo, n, T, ldt, sT, inv, sI, X, ldx, sX, batch, tri);
+}
+hipError_t launch_block_solve(hipStream_t st, bool upper, int wo, int n, const zflt *T, int64_t ldt, int64_t sT,
+                              const zflt *inv, int64_t sI, zflt *X, int64_t ldx, int64_t sX, int batch, int tri) {
+    return block_solve<float>(st, upper, wo, n, T, ldt, sT, inv, sI, X, ldx, sX, batch, tri);
+}
+
+#define GW_SOLVE(OP)                             \
+    do {                                         \
+        if (variant == 0) OP(double, false);     \
+        else if (variant == 1) OP(double, true); \
+        else if (variant == 2) OP(float, false); \
+        else OP(float, true);                    \
+    } while (0)
+
+hipError_t launch_block_solve_group(hipStream_t st, int variant, const GemmItem *items, int n_items, int64_t n_tiles) {
     if (n_tiles > INT32_MAX) return hipErrorInvalidValue;
     const dim3 grid((unsigned)n_tiles), blk(256);
-    if (upper) hipLaunchKernelGGL((k_block_solve_group<true>), grid, blk, 0, st, items, n_items, n_tiles);
-    else hipLaunchKernelGGL((k_block_solve_group<false>), grid, blk, 0, st, items, n_items, n_tiles);
+#define GW_RUN(T, UP) hipLaunchKernelGGL((k_block_solve_group<T, UP>), grid, blk, 0, st, items, n_items, n_tiles)
+    GW_SOLVE(GW_RUN);
+#undef GW_RUN
     return hipGetLastError();
 }
-int block_solve_occupancy(bool upper) {
+int block_solve_occupancy(int variant) {
     int occ = 0;
-    const hipError_t e =
-        upper ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_block_solve_group<true>, 256, 0)
-              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_block_solve_group<false>, 256, 0);
+    hipError_t e = hipErrorInvalidValue;
+#define GW_OCC(T, UP) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_block_solve_group<T, UP>, 256, 0)
+    GW_SOLVE(GW_OCC);
+#undef GW_OCC
     return e == hipSuccess && occ > 0 ? occ : 2;
 }
+int block_solve_columns(int variant) { return 16 * (variant < 2 ? Tv<double>::NH : Tv<float>::NH); }
 
 }  // namespace gwk
