@@ -832,21 +832,23 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_queue(const GemmItem *__restr
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__device__ inline unsigned short bf16_rne(float x) {
-    unsigned u = __float_as_uint(x);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-__device__ inline float bf16_to_f(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
-
 constexpr int XK = 32;  // complex k per stage
 
-__global__ __launch_bounds__(256, 1) void k_cgemm_bf16x(int M, int N, int K, float alpha, const float *__restrict__ A,
+// What bounds it: per stage a wave has 96 products of 16 cycles, and beside them
+// the splitting of 32 values per thread, which the matrix cores do not hide.  So
+// the terms are rounded two at a time (v_cvt_pk_bf16_f32), the operands come in
+// 16-byte loads where they lie inside the matrix, and a row's four 16-byte runs
+// of k are kept in the order run ^ (row / 4) % 4, which spreads sixteen rows'
+// reads (and B's writes) over all banks; two workgroups per CU, so that no
+// accumulator is moved to the other half of the register file.  655 products,
+// 128 frequencies: 105 us a launch (108.5 with single roundings, element loads
+// and unswizzled rows).
+__global__ __launch_bounds__(256, 2) void k_cgemm_bf16x(int M, int N, int K, float alpha, const float *__restrict__ A,
                                                         int64_t lda, int64_t sA, const float *B, int64_t ldb,
                                                         int64_t sB, float beta, float *C, int64_t ldc, int64_t sC) {
     // planes [term 0..2][part re/im][row or col 0..63][k 0..31] of bf16
-    __shared__ unsigned short As[3][2][64][XK];
-    __shared__ unsigned short Bs[3][2][64][XK];
+    __shared__ __align__(16) unsigned short As[3][2][64][XK];
+    __shared__ __align__(16) unsigned short Bs[3][2][64][XK];
     const int bz = blockIdx.z;
     A += (int64_t)bz * sA * 2;
     B += (int64_t)bz * sB * 2;
@@ -863,50 +865,65 @@ __global__ __launch_bounds__(256, 1) void k_cgemm_bf16x(int M, int N, int K, flo
     const int a_row = tid >> 2, a_k = (tid & 3) * 8;
     const int b_col = tid & 63, b_k = (tid >> 6) * 8;
     float ar[8], ai[8], br[8], bi[8];
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
     auto gload = [&](int k0) {
-        const int gr = m0 + a_row;
+        const int gr = m0 + a_row, gc = n0 + b_col;
+        if (gr < M && k0 + a_k + 8 <= K) {
+            const f4u *p = (const f4u *)(A + ((int64_t)gr * lda + k0 + a_k) * 2);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int gk = k0 + a_k + c;
-            if (gr < M && gk < K) {
-                const float *p = A + ((int64_t)gr * lda + gk) * 2;
-                ar[c] = p[0];
-                ai[c] = p[1];
-            } else {
-                ar[c] = 0.f;
-                ai[c] = 0.f;
+            for (int c = 0; c < 4; ++c) {
+                const f4u v = p[c];
+                ar[2 * c] = v.x;
+                ai[2 * c] = v.y;
+                ar[2 * c + 1] = v.z;
+                ai[2 * c + 1] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int gk = k0 + a_k + c;
+                ar[c] = ai[c] = 0.f;
+                if (gr < M && gk < K) {
+                    const float *p = A + ((int64_t)gr * lda + gk) * 2;
+                    ar[c] = p[0];
+                    ai[c] = p[1];
+                }
             }
         }
-        const int gc = n0 + b_col;
+        if (k0 + XK <= K) {  // (a column past N: the last one's values, not stored)
+            const float *p = B + ((int64_t)(k0 + b_k) * ldb + min(gc, N - 1)) * 2;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int gk = k0 + b_k + c;
-            if (gc < N && gk < K) {
-                const float *p = B + ((int64_t)gk * ldb + gc) * 2;
-                br[c] = p[0];
-                bi[c] = p[1];
-            } else {
-                br[c] = 0.f;
-                bi[c] = 0.f;
+            for (int c = 0; c < 8; ++c) {
+                br[c] = p[2 * c * ldb];
+                bi[c] = p[2 * c * ldb + 1];
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const int gk = k0 + b_k + c;
+                br[c] = bi[c] = 0.f;
+                if (gc < N && gk < K) {
+                    const float *p = B + ((int64_t)gk * ldb + gc) * 2;
+                    br[c] = p[0];
+                    bi[c] = p[1];
+                }
             }
         }
     };
+    // eight k of one row or column: x = h + m + l, term by term
     auto split_store = [&](unsigned short (*P)[2][64][XK], int part, int rc, int k, const float *x) {
-        unsigned short h[8], mm[8], l[8];
+        bf16x8 t[3];
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-            h[c] = bf16_rne(x[c]);
-            const float r1 = x[c] - bf16_to_f(h[c]);
-            mm[c] = bf16_rne(r1);
-            l[c] = bf16_rne(r1 - bf16_to_f(mm[c]));
+            t[0][c] = (__bf16)x[c];
+            const float r1 = x[c] - (float)t[0][c];
+            t[1][c] = (__bf16)r1;
+            t[2][c] = (__bf16)(r1 - (float)t[1][c]);
         }
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            P[0][part][rc][k + c] = h[c];
-            P[1][part][rc][k + c] = mm[c];
-            P[2][part][rc][k + c] = l[c];
-        }
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8 *>(&P[q][part][rc][k ^ (8 * ((rc >> 2) & 3))]) = t[q];
     };
+    const int fk = 8 * ((lane >> 4) ^ ((lane >> 2) & 3));  // where a fragment row's run of k lies
     gload(0);
     for (int k0 = 0; k0 < K; k0 += XK) {
         __syncthreads();
@@ -925,7 +942,7 @@ __global__ __launch_bounds__(256, 1) void k_cgemm_bf16x(int M, int N, int K, flo
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
                     fb[t][part][j] = *reinterpret_cast<const bf16x8 *>(
-                        &Bs[t][part][wn * 32 + j * 16 + (lane & 15)][8 * (lane >> 4)]);
+                        &Bs[t][part][wn * 32 + j * 16 + (lane & 15)][fk]);
         // A term t pairs with B terms q, t + q <= 2
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
@@ -935,7 +952,7 @@ __global__ __launch_bounds__(256, 1) void k_cgemm_bf16x(int M, int N, int K, flo
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
                     fa[part][i] = *reinterpret_cast<const bf16x8 *>(
-                        &As[t][part][wm * 32 + i * 16 + (lane & 15)][8 * (lane >> 4)]);
+                        &As[t][part][wm * 32 + i * 16 + (lane & 15)][fk]);
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 if (t + q > 2) continue;
