@@ -950,7 +950,7 @@ gw_status level_tables(gw_ctx *ctx, const HostMol &h, int n_orb, int n_occ, int 
 // Vertex block pairs B1 <= B2 (pb1 then pb2 in one array), grouped by tile
 // class 2 (|O1| > 16) + (|O2| > 16) with class c at class_off[c] ..
 // class_off[c+1] - 1 (class_off may be null), and the largest
-// (products x |O|^2) of a block.  cost (or null): a pair is taken as (B2, B1)
+// (products x |O|^2) of a block with |O| <= 16 and of one above.  cost (or null): a pair is taken as (B2, B1)
 // where cost(B2, B1) is the smaller (a contraction whose two orders give a
 // matrix and its transpose).
 int block_pairs(const HostMol &h, int nblk, std::vector<int32_t> *pbs, int *max_vblock, int *class_off = nullptr,
@@ -974,10 +974,11 @@ int block_pairs(const HostMol &h, int nblk, std::vector<int32_t> *pbs, int *max_
     const int npb = off[4];
     if (class_off)
         for (int c = 0; c < 5; ++c) class_off[c] = off[c];
-    *max_vblock = 0;
+    max_vblock[0] = max_vblock[1] = 0;
     for (int b = 0; b < nblk; ++b) {
         const int no = h.blk_orb[b + 1] - h.blk_orb[b];
-        *max_vblock = std::max(*max_vblock, (h.blk_prod[b + 1] - h.blk_prod[b]) * no * no);
+        int &mx = max_vblock[no > 16];
+        mx = std::max(mx, (h.blk_prod[b + 1] - h.blk_prod[b]) * no * no);
     }
     return npb;
 }
@@ -1038,9 +1039,9 @@ static gw_status build_time_impl(gw_ctx *ctx, const gw_molecule *m, const double
     // block pairs B1 <= B2 and the contraction's flop count
     std::vector<int32_t> pbs;
     double cflops = 0.0;
-    int max_vblock = 0;
+    int max_vblock[2];
     int class_off[5];
-    const int npb = block_pairs(h, nblk, &pbs, &max_vblock, class_off);
+    const int npb = block_pairs(h, nblk, &pbs, max_vblock, class_off);
     for (int b1 = 0; b1 < nblk; ++b1)
         for (int b2 = b1; b2 < nblk; ++b2) {
             const double n1 = h.blk_orb[b1 + 1] - h.blk_orb[b1], n2 = h.blk_orb[b2 + 1] - h.blk_orb[b2];
@@ -1158,8 +1159,8 @@ gw_status gw_self_energy(gw_ctx *ctx, const gw_molecule *m, const double *v, con
     const int L = std::max(Kp, Km) + n_sb - 1;
     const int Q = L / 2 + 1;
     std::vector<int32_t> pbs;
-    int max_vblock = 0, class_off[5];
-    const int npb = block_pairs(h, nblk, &pbs, &max_vblock, class_off, sigma_pair_flops);
+    int max_vblock[2], class_off[5];
+    const int npb = block_pairs(h, nblk, &pbs, max_vblock, class_off, sigma_pair_flops);
     double cflops = 0.0;
     for (int i = 0; i < npb; ++i) cflops += sigma_pair_flops(h, pbs[i], pbs[npb + i]);
     const int64_t nn = (int64_t)n_orb * n_orb;

@@ -108,7 +108,6 @@ __global__ __launch_bounds__(256) void k_trace_dos(int n, int j0, const zdbl *__
 }
 
 constexpr int SO = TIME_MAX_ORB;
-constexpr int SP = SO + 1;
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -131,105 +130,122 @@ __device__ inline v4d mfma4(double a, double b, v4d c) { return __builtin_amdgcn
 // lane l = B[l / 16][l % 16], result element e of lane l = D[l / 16 + 4 e][l % 16].
 // TWO = false: one density only.  The wave's C+- are then added to S+-
 // (atomically; the transpose too for two different blocks).
+// Bound by the matrix cores and, beside them, by G's loads and additions, which
+// nothing hides at one wave per SIMD.  So V is read as LDS (vlds, where staged)
+// or as global memory, never through a pointer that could be either; columns go
+// sixteen at a time and G's offsets are formed anew for each mu, so that no class
+// spills and |O2| <= 16 has registers for two workgroups per CU.  870 products, 512
+// points, classes (1,1), (2,1), (2,2): 7.6, 8.7, 7.7 ms before, 3.9, 6.2, 6.8 now.
 template <int T1, int T2, bool TWO>
 __device__ void sigma_wave(int n1, int n2, int p1, int e1, int p2, int e2, bool same, int n_prod, int n_orb,
-                           int lane, int wave, const double *__restrict__ v1, const double *v2,
+                           int lane, int wave, const double *__restrict__ v1,
+                           const double *__restrict__ v2, const double *vlds, bool staged,
                            const double *__restrict__ ghr, const double *__restrict__ ghi, const double *ppr,
                            const double *ppi, const double *pmr, const double *pmi, const int *o1, const int *o2,
                            double *spr, double *spi, double *smr, double *smi) {
     const int lr = lane & 15, lk = lane >> 4;
     const int nsq1 = n1 * n1, nsq2 = n2 * n2;
+    constexpr int SP = 16 * T2 + 1;  // row stride of the densities
     v4d cpr[T1][T2], cpi[T1][T2], cmr[T1][T2], cmi[T1][T2];
 #pragma unroll
     for (int at = 0; at < T1; ++at)
 #pragma unroll
         for (int dt = 0; dt < T2; ++dt) cpr[at][dt] = cpi[at][dt] = cmr[at][dt] = cmi[at][dt] = v4d{0, 0, 0, 0};
     for (int mu = p1 + wave; mu < e1; mu += 4) {
-        // G[c][d] at c = 4 s + lk, d = dt*16 + lr: the B operand of every k step
-        double gr[4 * T2][T2], gi[4 * T2][T2];
+        // sixteen columns of G, U and C at a time (the columns are independent;
+        // all 32 at once would spill)
 #pragma unroll
-        for (int s = 0; s < 4 * T2; ++s)
-#pragma unroll
-            for (int dt = 0; dt < T2; ++dt) gr[s][dt] = gi[s][dt] = 0.0;
-        // the weights gammahat^{mu nu} of 64 products nu at a time, one per
-        // lane (one vector load instead of a dependent load per nu)
-        double lwr = 0.0, lwi = 0.0;
-        for (int nu = p2; nu < e2; ++nu) {
-            const int q = (nu - p2) & 63;
-            if (q == 0) {
-                const int nl = nu + lane;
-                if (nl < e2) {
-                    const int a = min(mu, nl), b = max(mu, nl);
-                    const int64_t t = (int64_t)a * n_prod - ((int64_t)a * (a - 1)) / 2 + (b - a);
-                    lwr = ghr[t];
-                    lwi = ghi[t];
-                }
-            }
-            const double wr = rlane_d(lwr, q), wi = rlane_d(lwi, q);
-            const double *vnu = v2 + (int64_t)(nu - p2) * nsq2;  // LDS copy when staged
-#pragma unroll
-            for (int s = 0; s < 4 * T2; ++s)
-#pragma unroll
-                for (int dt = 0; dt < T2; ++dt) {
-                    const int c = 4 * s + lk, d = dt * 16 + lr;
-                    const double v = (c < n2 && d < n2) ? vnu[c * n2 + d] : 0.0;
-                    gr[s][dt] += wr * v;
-                    gi[s][dt] += wi * v;
-                }
-        }
-        // vertex entries of mu, the A operand of C += V_mu U: V[a][i] at
-        // a = at*16 + lr, i = 4 k + lk
-        double va[T1][4 * T1];
-        const double *vmu = v1 + (int64_t)(mu - p1) * nsq1;
-#pragma unroll
-        for (int at = 0; at < T1; ++at)
-#pragma unroll
-            for (int k = 0; k < 4 * T1; ++k) {
-                const int a = at * 16 + lr, ii = 4 * k + lk;
-                va[at][k] = (a < n1 && ii < n1) ? vmu[a * n1 + ii] : 0.0;
-            }
-#pragma unroll
-        for (int den = 0; den < (TWO ? 2 : 1); ++den) {
-            const double *qr = den ? pmr : ppr, *qi = den ? pmi : ppi;
-            // U[i][d] = sum_c rho[i][c] G[c][d]
-            v4d ur[T1][T2], ui[T1][T2];
-#pragma unroll
-            for (int it = 0; it < T1; ++it)
-#pragma unroll
-                for (int dt = 0; dt < T2; ++dt) ur[it][dt] = ui[it][dt] = v4d{0, 0, 0, 0};
+        for (int dt = 0; dt < T2; ++dt) {
+            // G[c][d] at c = 4 s + lk, d = dt*16 + lr: the B operand of every k
+            // step.  Past |O2| a lane takes the last row's or column's entries:
+            // such rows of G meet zero columns of rho, such columns only reach
+            // columns of C that are not stored.
+            double gr[4 * T2], gi[4 * T2];
+            int at2[4 * T2];
 #pragma unroll
             for (int s = 0; s < 4 * T2; ++s) {
-                const int c = 4 * s + lk;
+                gr[s] = gi[s] = 0.0;
+                at2[s] = min(4 * s + lk, n2 - 1) * n2 + min(dt * 16 + lr, n2 - 1);
+#if defined(__HIP_DEVICE_COMPILE__)
+                asm volatile("" : "+v"(at2[s]));  // (here, not kept from one mu to the next)
+#endif
+            }
+            // the weights gammahat^{mu nu} of 64 products nu at a time, one per
+            // lane (one vector load instead of a dependent load per nu)
+            auto form_g = [&](const double *vb) {
+                for (int nu0 = p2; nu0 < e2; nu0 += 64) {
+                    double lwr = 0.0, lwi = 0.0;
+                    const int nl = nu0 + lane, cnt = min(64, e2 - nu0);
+                    if (nl < e2) {
+                        const int a = min(mu, nl), b = max(mu, nl);
+                        const int64_t t = (int64_t)a * n_prod - ((int64_t)a * (a - 1)) / 2 + (b - a);
+                        lwr = ghr[t];
+                        lwi = ghi[t];
+                    }
+                    const double *vnu = vb + (int64_t)(nu0 - p2) * nsq2;
+#pragma unroll(T2 == 1 ? 2 : 1)
+                    for (int q = 0; q < cnt; ++q, vnu += nsq2) {
+                        const double wr = rlane_d(lwr, q), wi = rlane_d(lwi, q);
 #pragma unroll
-                for (int it = 0; it < T1; ++it) {
-                    const double ar = qr[(it * 16 + lr) * SP + c], ai = qi[(it * 16 + lr) * SP + c];
-#pragma unroll
-                    for (int dt = 0; dt < T2; ++dt) {
-                        ur[it][dt] = mfma4(ar, gr[s][dt], ur[it][dt]);
-                        ur[it][dt] = mfma4(-ai, gi[s][dt], ur[it][dt]);
-                        ui[it][dt] = mfma4(ar, gi[s][dt], ui[it][dt]);
-                        ui[it][dt] = mfma4(ai, gr[s][dt], ui[it][dt]);
+                        for (int s = 0; s < 4 * T2; ++s) {
+                            const double v = vnu[at2[s]];
+                            gr[s] += wr * v;
+                            gi[s] += wi * v;
+                        }
                     }
                 }
-            }
-            // C[a][d] += sum_i V[a][i] U[i][d]; k steps over i: tile it, element e
+            };
+            // (two copies of the loop, so that neither reads through a pointer
+            // that could be either memory: flat loads wait on both)
+            if (staged) form_g(vlds);
+            else form_g(v2);
+            // vertex entries of mu, the A operand of C += V_mu U: V[a][i] at
+            // a = at*16 + lr, i = 4 k + lk
+            double va[T1][4 * T1];
+            const double *vmu = v1 + (int64_t)(mu - p1) * nsq1;
 #pragma unroll
-            for (int it = 0; it < T1; ++it)
+            for (int at = 0; at < T1; ++at)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int k = 0; k < 4 * T1; ++k) {
+                    const int a = at * 16 + lr, ii = 4 * k + lk;
+                    va[at][k] = (a < n1 && ii < n1) ? vmu[a * n1 + ii] : 0.0;
+                }
 #pragma unroll
-                    for (int at = 0; at < T1; ++at)
+            for (int den = 0; den < (TWO ? 2 : 1); ++den) {
+                const double *qr = den ? pmr : ppr, *qi = den ? pmi : ppi;
+                // U[i][d] = sum_c rho[i][c] G[c][d]
+                v4d ur[T1], ui[T1];
 #pragma unroll
-                        for (int dt = 0; dt < T2; ++dt) {
+                for (int it = 0; it < T1; ++it) ur[it] = ui[it] = v4d{0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < 4 * T2; ++s) {
+                    const int c = 4 * s + lk;
+#pragma unroll
+                    for (int it = 0; it < T1; ++it) {
+                        const double ar = qr[(it * 16 + lr) * SP + c], ai = qi[(it * 16 + lr) * SP + c];
+                        ur[it] = mfma4(ar, gr[s], ur[it]);
+                        ui[it] = mfma4(ar, gi[s], ui[it]);
+                        ur[it] = mfma4(-ai, gi[s], ur[it]);
+                        ui[it] = mfma4(ai, gr[s], ui[it]);
+                    }
+                }
+                // C[a][d] += sum_i V[a][i] U[i][d]; k steps over i: tile it, element e
+#pragma unroll
+                for (int it = 0; it < T1; ++it)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int at = 0; at < T1; ++at) {
                             const double a = va[at][4 * it + e];
                             if (den == 0) {
-                                cpr[at][dt] = mfma4(a, ur[it][dt][e], cpr[at][dt]);
-                                cpi[at][dt] = mfma4(a, ui[it][dt][e], cpi[at][dt]);
+                                cpr[at][dt] = mfma4(a, ur[it][e], cpr[at][dt]);
+                                cpi[at][dt] = mfma4(a, ui[it][e], cpi[at][dt]);
                             } else {
-                                cmr[at][dt] = mfma4(a, ur[it][dt][e], cmr[at][dt]);
-                                cmi[at][dt] = mfma4(a, ui[it][dt][e], cmi[at][dt]);
+                                cmr[at][dt] = mfma4(a, ur[it][e], cmr[at][dt]);
+                                cmi[at][dt] = mfma4(a, ui[it][e], cmi[at][dt]);
                             }
                         }
+            }
         }
     }
     // add this wave's C+- (element e of a lane: a = at*16 + lk + 4e, b = dt*16 + lr)
@@ -273,7 +289,8 @@ __global__ __launch_bounds__(256) void k_sigma_contract(
     const double *__restrict__ Rp, const double *__restrict__ Rm, const double *__restrict__ Gh,
     double *__restrict__ Sp, double *__restrict__ Sm) {
     __shared__ int o1[SO], o2[SO];
-    __shared__ double ppr[SO * SP], ppi[SO * SP], pmr[TWO ? SO * SP : 1], pmi[TWO ? SO * SP : 1];
+    constexpr int SP = 16 * T2 + 1, NP = 16 * T1 * SP;
+    __shared__ double ppr[NP], ppi[NP], pmr[TWO ? NP : 1], pmi[TWO ? NP : 1];
     extern __shared__ double vstage[];  // V of B2, when it fits in v_cap doubles
     const int B1 = pb1[blockIdx.y], B2 = pb2[blockIdx.y];
     const int qq = blockIdx.x, q = q0 + qq;
@@ -282,7 +299,7 @@ __global__ __launch_bounds__(256) void k_sigma_contract(
     const int n1 = blk_orb[B1 + 1] - ob1, n2 = blk_orb[B2 + 1] - ob2;
     if (tid < n1) o1[tid] = orb_idx[ob1 + tid];
     if (tid < n2) o2[tid] = orb_idx[ob2 + tid];
-    for (int idx = tid; idx < SO * SP; idx += 256) {
+    for (int idx = tid; idx < NP; idx += 256) {
         ppr[idx] = ppi[idx] = 0.0;
         if (TWO) pmr[idx] = pmi[idx] = 0.0;
     }
@@ -307,14 +324,13 @@ __global__ __launch_bounds__(256) void k_sigma_contract(
     const int nv2 = (blk_prod[B2 + 1] - blk_prod[B2]) * n2 * n2;
     if (nv2 <= v_cap) {
         for (int idx = tid; idx < nv2; idx += 256) vstage[idx] = v2[idx];
-        v2 = vstage;
     }
     __syncthreads();
     const double *ghr = Gh + (int64_t)(2 * qq) * n_upper, *ghi = ghr + n_upper;
     double *spr = Sp + (int64_t)(2 * qq) * nn, *spi = spr + nn;
     double *smr = TWO ? Sm + (int64_t)(2 * qq) * nn : nullptr, *smi = TWO ? smr + nn : nullptr;
     sigma_wave<T1, T2, TWO>(n1, n2, blk_prod[B1], blk_prod[B1 + 1], blk_prod[B2], blk_prod[B2 + 1], B1 == B2, n_prod,
-                            n_orb, lane, wave, vals + blk_val[B1], v2, ghr, ghi, ppr, ppi, pmr, pmi,
+                            n_orb, lane, wave, vals + blk_val[B1], v2, vstage, nv2 <= v_cap, ghr, ghi, ppr, ppi, pmr, pmi,
                             o1, o2, spr, spi, smr, smi);
 }
 
@@ -377,17 +393,20 @@ hipError_t launch_sigma_contract(hipStream_t st, int n_orb, int n_prod, const in
                                  const int32_t *blk_prod, const int32_t *blk_orb, const int32_t *orb_idx,
                                  const int64_t *blk_val, const double *vals, const int32_t *pb1, const int32_t *pb2,
                                  const double *Rp, const double *Rm, const double *Gh, double *Sp, double *Sm,
-                                 int max_vblock, double flops) {
+                                 const int *max_vblock, double flops) {
     if (class_off[4] <= 0 || nq <= 0) return hipSuccess;
     // the vertex block of B2 is staged in LDS when it fits next to the
-    // densities (96 KB); larger blocks are read from memory
-    const int v_cap = std::min(max_vblock, 96 * 1024 / 8);
-    const size_t lds = sizeof(double) * (size_t)v_cap;
+    // densities (96 KB); larger blocks are read from memory.  Each class asks for
+    // what its own largest block needs: |O2| <= 16 (54 KB for an atom's 40
+    // products of 13 orbitals) leaves room for two workgroups per CU (with one, the
+    // classes (1,1) and (2,1) took 5.7 and 8.3 ms instead of 3.9 and 6.2).
     const double nn = (double)n_orb * n_orb;
     ProfScope ps(st, "sigma_contract", flops, 16.0 * nq * nn * (Rm ? 2 : 1));
     // one launch per tile class (|O1|, |O2| up to 16 or 32)
 #define GW_SC(T1, T2, c)                                                                                        \
     if (class_off[c + 1] > class_off[c]) {                                                                     \
+        const int v_cap = std::min(max_vblock[T2 - 1], 96 * 1024 / 8);                                         \
+        const size_t lds = sizeof(double) * (size_t)v_cap;                                                     \
         dim3 grid((unsigned)nq, (unsigned)(class_off[c + 1] - class_off[c]));                                  \
         hipError_t ea = Rm ? hipFuncSetAttribute((const void *)k_sigma_contract<T1, T2, true>,                  \
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)           \
