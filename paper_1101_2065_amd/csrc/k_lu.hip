@@ -371,12 +371,19 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
         p->re = v.x;
         p->im = v.y;
     };
-    // x - l u in two fused steps per part
+    // x - l u: FP64 in two fused steps per part; FP32 with l u formed first, so
+    // that a step rounds at x's size once, not twice (the refinement's last
+    // error is a power of the FP32 factors')
     auto submul = [](V2 &x, V2 l, V2 u) {
-        x.x = fma(-l.x, u.x, x.x);
-        x.x = fma(l.y, u.y, x.x);
-        x.y = fma(-l.x, u.y, x.y);
-        x.y = fma(-l.y, u.x, x.y);
+        if constexpr (sizeof(T) == 8) {
+            x.x = fma(-l.x, u.x, x.x);
+            x.x = fma(l.y, u.y, x.x);
+            x.y = fma(-l.x, u.y, x.y);
+            x.y = fma(-l.y, u.x, x.y);
+        } else {
+            x.x -= fma(l.x, u.x, -(l.y * u.y));
+            x.y -= fma(l.x, u.y, l.y * u.x);
+        }
     };
 
     // slab q & 1: columns [c0, c0 + 4) of this wave's rows 512 r ..; rows and
