@@ -211,6 +211,10 @@ def kernel_roofline(stats):
         achieved = d["flops"] / sec / 1e12
         rec = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                "flops_per_launch": d["flops"] / d["launches"]}
+        if d["name"].startswith("zgemm3m"):
+            # three real products execute 6 M N K of the 8 M N K counted, so frac
+            # can pass 1; this is what the matrix cores run
+            rec["executed"] = 0.75 * achieved
     else:
         achieved = d["bytes"] / sec / 1e9
         rec = {"bound": "hbm", "achieved": achieved, "peak": 8000.0, "unit": "GB/s", "frac": achieved / 8000.0,
@@ -889,8 +893,8 @@ def run_c4(args, gw, gs, torch):
 
 # ---------------------------------------------------------------------- profiles
 # Kernel whose HBM traffic the roofline reports, and the source it is built from.
-TRAFFIC_KERNEL = "k_gemm<double, true, true, 2, 1, 8, 5, 1, true, false>"
-TRAFFIC_CLASS = "zgemm3m_64x32"  # the same kernel in the library's live timing
+TRAFFIC_KERNEL = "k_zgemm<4, 2, 2, true, true>"
+TRAFFIC_CLASS = "zgemm3m_128x64"  # the same kernel in the library's live timing
 TRAFFIC_FILE = os.path.join(HERE, "profiles", "hbm_traffic.json")
 COPY_BYTES = 1 << 30
 
