@@ -102,7 +102,7 @@ hipError_t launch_block_solve(hipStream_t st, bool upper, int wo, int n, const z
                               const zflt *inv, int64_t sI, zflt *X, int64_t ldx, int64_t sX, int batch, int tri);
 hipError_t launch_block_solve_group(hipStream_t st, int variant, const GemmItem *items, int n_items, int64_t n_tiles);
 int block_solve_occupancy(int variant);
-int block_solve_columns(int variant);  // columns of a strip
+int block_solve_columns();  // columns of a strip
 // One launch of `n_items` products (descriptors on the device), `n_tiles`
 // tiles in all: with `queue` (eight counters, zero) a persistent grid of
 // `grid` workgroups pulling tiles from per-XCD work queues, without it one

@@ -1382,7 +1382,7 @@ int gemm_queue_occupancy(int key) {
 void gemm_queue_tile(int key, int *bm, int *bn) {
     if (key / 4 == QK_SOLVE) {  // a strip of all the block's rows
         *bm = 256;
-        *bn = block_solve_columns(key % 4);
+        *bn = block_solve_columns();
         return;
     }
     const QShape q = qshape(key);

@@ -6,20 +6,25 @@
 // Panel by panel, X_p <- T_pp^{-1} X_p, then X_q -= T_qp X_p for the panels q
 // still to come.  As separate products these were bound by HBM: each K = 64
 // update reads and writes all the rows below it (44-55 TF in 8MNK).  Here a
-// workgroup keeps a strip of 32 columns (FP32: 64) of all 256 rows in registers, so X is
+// workgroup keeps a strip of 32 columns of all 256 rows in registers, so X is
 // read and written once and the products run from LDS: wave w holds rows
 // 16 w .. 16 w + 15 of every panel, which gives the four waves equal shares of
 // every step.  X_p goes through LDS as the matrix-core operand B (the register
 // layout of a result is already that order: one conflict-free 16-byte store per
-// value); the operand A comes from the factors in L2, four steps ahead.  The
-// arithmetic, and its order, is that of the separate products.
+// value); the operand A comes from the factors in L2, four steps ahead.
 // 256 rows, 2000 columns, 120 matrices: 1.07 ms, 74 TF in 8MNK (62 TF for 8
 // matrices, whose 504 strips just fill the chip); bound by the matrix cores (103
 // TF in this count) and, at two waves per SIMD, the latency around the barriers
 // of its ten steps.  n = 1100: 25 ms of launches where the products took 32.
-// Wider strips would leave one wave per SIMD (registers).  FP32, 517 and 655
-// rows, 128 frequencies, three solves: 4.2 ms of launches for 6.5 of FP32
-// products, 5.8 for 7.2 of split-BF16 ones.
+// Wider strips would leave one wave per SIMD (registers).
+//
+// FP32 has the same products in FP64 and rounds once per panel: the error of the
+// 32-bit forms after refinement is a power of their first solution's.  With the
+// sums in FP32, 128 roundings a panel, the split-BF16 form's error at 655 rows
+// (tolerance 1e-10, 14 chains) was 9.3e-12, against 5.4e-12 by separate
+// split-BF16 products and 4.4e-12 so.  It costs matrix-core time: 517 and 655
+// rows, 128 frequencies, three solves, 5.1 and 7.4 ms of launches for 4.3 and
+// 5.9; the separate products took 6.5 (FP32) and 7.2 (split BF16).
 #include "gw_internal.h"
 #include "gw_prof.h"
 #include "k_mfma.h"
@@ -38,67 +43,49 @@ template <>
 struct Tv<double> {
     typedef double v2 __attribute__((ext_vector_type(2)));
     typedef double v2u __attribute__((ext_vector_type(2), aligned(8)));
-    static constexpr int NH = 2;  // sixteens of columns in a strip
 };
 template <>
 struct Tv<float> {
     typedef float v2 __attribute__((ext_vector_type(2)));
     typedef float v2u __attribute__((ext_vector_type(2), aligned(4)));
-    static constexpr int NH = 4;
 };
+typedef Tv<double>::v2 zd2;
+typedef Mfma<double>::v4 v4;
+constexpr int NH = 2;  // sixteens of columns in a strip
 
-// c = A B over 64 k for this wave's 16 rows and the strip's columns: FP64 as
-// three real products (ac, bd, (a + b)(c + d)), FP32 as four.  row: the lane's
-// row of A; a already holds its first four steps (k = lane / 16 + 4 q).
-template <typename T>
+// c = A B over 64 k for this wave's 16 rows and the strip's columns, as three
+// real FP64 products (ac, bd, (a + b)(c + d)).  row: the lane's row of A; a
+// already holds its first four steps (k = lane / 16 + 4 q).
 struct Acc {
-    typedef typename Mfma<T>::v4 v4;
-    static constexpr bool M3 = sizeof(T) == 8;
-    v4 r[Tv<T>::NH], i[Tv<T>::NH], s[M3 ? Tv<T>::NH : 1];
-    __device__ __forceinline__ T re(int h, int e) const { return M3 ? r[h][e] - i[h][e] : r[h][e]; }
-    __device__ __forceinline__ T im(int h, int e) const {
-        return M3 ? s[M3 ? h : 0][e] - r[h][e] - i[h][e] : i[h][e];
-    }
+    v4 r[NH], i[NH], s[NH];
+    __device__ __forceinline__ double re(int h, int e) const { return r[h][e] - i[h][e]; }
+    __device__ __forceinline__ double im(int h, int e) const { return s[h][e] - r[h][e] - i[h][e]; }
 };
 template <typename V2, typename G2>
 __device__ __forceinline__ void load4(V2 (&a)[4], const G2 *row, int k0, int lk, int kmax) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) a[q] = row[min(k0 + 4 * q + lk, kmax)];
 }
-template <typename T, typename G2, typename V2>
-__device__ __forceinline__ void mul64(Acc<T> &c, V2 (&a)[4], const G2 *row, int lk, int lane, int kmax, const V2 *b) {
-    typedef typename Mfma<T>::v4 v4;
-    constexpr int NH = Tv<T>::NH;
+template <typename G2, typename V2>
+__device__ __forceinline__ void mul64(Acc &c, V2 (&a)[4], const G2 *row, int lk, int lane, int kmax, const zd2 *b) {
 #pragma unroll
-    for (int j = 0; j < NH; ++j) {
-        c.r[j] = c.i[j] = v4{0, 0, 0, 0};
-        if constexpr (Acc<T>::M3) c.s[j] = v4{0, 0, 0, 0};
-    }
+    for (int j = 0; j < NH; ++j) c.r[j] = c.i[j] = c.s[j] = v4{0, 0, 0, 0};
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
         V2 n[4];
         if (h < 3) load4(n, row, 16 * (h + 1), lk, kmax);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            V2 bv[NH];
+            zd2 bv[NH];
 #pragma unroll
             for (int j = 0; j < NH; ++j) bv[j] = b[(NH * (4 * h + q) + j) * 64 + lane];
+            const double ax = a[q].x, ay = a[q].y, sa = ax + ay;
 #pragma unroll
-            for (int j = 0; j < NH; ++j) c.r[j] = Mfma<T>::op(a[q].x, bv[j].x, c.r[j]);
-            if constexpr (Acc<T>::M3) {
-                const T sa = a[q].x + a[q].y;
+            for (int j = 0; j < NH; ++j) c.r[j] = Mfma<double>::op(ax, bv[j].x, c.r[j]);
 #pragma unroll
-                for (int j = 0; j < NH; ++j) c.i[j] = Mfma<T>::op(a[q].y, bv[j].y, c.i[j]);
+            for (int j = 0; j < NH; ++j) c.i[j] = Mfma<double>::op(ay, bv[j].y, c.i[j]);
 #pragma unroll
-                for (int j = 0; j < NH; ++j) c.s[j] = Mfma<T>::op(sa, bv[j].x + bv[j].y, c.s[j]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < NH; ++j) c.i[j] = Mfma<T>::op(a[q].x, bv[j].y, c.i[j]);
-#pragma unroll
-                for (int j = 0; j < NH; ++j) c.r[j] = Mfma<T>::op(-a[q].y, bv[j].y, c.r[j]);
-#pragma unroll
-                for (int j = 0; j < NH; ++j) c.i[j] = Mfma<T>::op(a[q].y, bv[j].x, c.i[j]);
-            }
+            for (int j = 0; j < NH; ++j) c.s[j] = Mfma<double>::op(sa, bv[j].x + bv[j].y, c.s[j]);
         }
         if (h < 3) {
 #pragma unroll
@@ -117,14 +104,13 @@ template <typename T, bool UPPER, typename G2>
 __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t ldt, const G2 *inv, G2 *X, int64_t ldx,
                                             int tri, int c0) {
     typedef typename Tv<T>::v2 V2;
-    constexpr int NH = Tv<T>::NH;
-    __shared__ V2 xb[NH * TNB * 16], yb[NH * TNB * 16];  // X_p before and after its diagonal block
+    __shared__ zd2 xb[NH * TNB * 16], yb[NH * TNB * 16];  // X_p before and after its diagonal block
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = lane & 15, lk = lane >> 4;
     const int np = (wo + TNB - 1) / TNB;
     // where a result's row goes as operand B: step k / 4, lanes 16 (k % 4) ..
     auto slot = [&](int h, int e) {
-        const int k = Mfma<T>::row(lane, e);
+        const int k = Mfma<double>::row(lane, e);
         return (NH * (4 * wave + (k >> 2)) + h) * 64 + 16 * (k & 3) + lr;
     };
     // panels in order of solution: step s is panel s, or np - 1 - s
@@ -136,7 +122,7 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t
         for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int row = TNB * p + 16 * wave + Mfma<T>::row(lane, e), col = c0 + 16 * h + lr;
+                const int row = TNB * p + 16 * wave + Mfma<double>::row(lane, e), col = c0 + 16 * h + lr;
                 x[p][h][e] = V2{0, 0};
                 if (p >= first && row < wo && col < n) x[p][h][e] = X[(int64_t)row * ldx + col];
             }
@@ -153,17 +139,17 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t
 #pragma unroll
         for (int h = 0; h < NH; ++h)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) xb[slot(h, e)] = x[p][h][e];
+            for (int e = 0; e < 4; ++e) xb[slot(h, e)] = zd2{(double)x[p][h][e].x, (double)x[p][h][e].y};
         __syncthreads();
-        Acc<T> c;
-        mul64<T>(c, a, di, lk, lane, TNB - 1, xb);
+        Acc c;
+        mul64(c, a, di, lk, lane, TNB - 1, xb);
 #pragma unroll
         for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const V2 y{c.re(h, e), c.im(h, e)};
-                yb[slot(h, e)] = y;
-                const int row = TNB * p + 16 * wave + Mfma<T>::row(lane, e), col = c0 + 16 * h + lr;
+                const V2 y{(T)c.re(h, e), (T)c.im(h, e)};
+                yb[slot(h, e)] = zd2{(double)y.x, (double)y.y};
+                const int row = TNB * p + 16 * wave + Mfma<double>::row(lane, e), col = c0 + 16 * h + lr;
                 if (row < wo && col < n) X[(int64_t)row * ldx + col] = y;
             }
         // the panels still to come
@@ -181,13 +167,13 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t
             load4(a, row, 0, lk, kmax);
             if (!have) __syncthreads();  // yb is complete
             have = true;
-            mul64<T>(c, a, row, lk, lane, kmax, yb);
+            mul64(c, a, row, lk, lane, kmax, yb);
 #pragma unroll
             for (int h = 0; h < NH; ++h)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    x[q][h][e].x = -c.re(h, e) + x[q][h][e].x;
-                    x[q][h][e].y = -c.im(h, e) + x[q][h][e].y;
+                    x[q][h][e].x = (T)(x[q][h][e].x - c.re(h, e));
+                    x[q][h][e].y = (T)(x[q][h][e].y - c.im(h, e));
                 }
         }
         // (no reader of xb or yb is left behind: the next step writes xb after
@@ -204,7 +190,7 @@ __global__ __launch_bounds__(256, 2) void k_block_solve(int wo, int n, const T *
     const int64_t n8 = nt / 8, t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;  // one matrix's strips on one XCD
     const int64_t b = t / gridDim.x;
     solve_strip<T, UPPER, G2>(wo, n, (const G2 *)T_ + b * sT, ldt, (const G2 *)inv_ + b * sI, (G2 *)X_ + b * sX, ldx,
-                              tri, (int)(t % gridDim.x) * 16 * Tv<T>::NH);
+                              tri, (int)(t % gridDim.x) * 16 * NH);
 }
 
 // Many batched block solves in one launch, a strip per workgroup, in the order
@@ -224,7 +210,7 @@ __global__ __launch_bounds__(256, 2) void k_block_solve_group(const GemmItem *__
     const GemmItem g = items[a];
     const int64_t r = t - g.t0, bz = r / g.tx;
     solve_strip<T, UPPER, G2>(g.M, g.N, (const G2 *)g.A + bz * g.sA, g.lda, (const G2 *)g.B + bz * g.sB,
-                              (G2 *)g.C + bz * g.sC, g.ldc, g.K, (int)(r - bz * g.tx) * 16 * Tv<T>::NH);
+                              (G2 *)g.C + bz * g.sC, g.ldc, g.K, (int)(r - bz * g.tx) * 16 * NH);
 }
 
 template <typename T, typename Z>
@@ -245,7 +231,7 @@ hipError_t block_solve(hipStream_t st, bool upper, int wo, int n, const Z *Tm, i
         return hipSuccess;
     }
     ProfScope ps(st, sizeof(T) == 4 ? "block_solve_c" : "block_solve", flops, 4.0 * sizeof(T) * wo * (double)n * batch);
-    const int cols = 16 * Tv<T>::NH;
+    const int cols = 16 * NH;
     const dim3 grid((unsigned)((n + cols - 1) / cols), (unsigned)batch);
     if (upper)
         hipLaunchKernelGGL((k_block_solve<T, true>), grid, dim3(256), 0, st, wo, n, (const T *)Tm, ldt, sT,
@@ -291,6 +277,6 @@ int block_solve_occupancy(int variant) {
 #undef GW_OCC
     return e == hipSuccess && occ > 0 ? occ : 2;
 }
-int block_solve_columns(int variant) { return 16 * (variant < 2 ? Tv<double>::NH : Tv<float>::NH); }
+int block_solve_columns() { return 16 * NH; }
 
 }  // namespace gwk
