@@ -275,6 +275,12 @@ __global__ __launch_bounds__(512) void k_getf2(int n, int kb, int w, Cx<T> *A, i
 // -> 142 us, 431 rows 375 -> 250, 2000 rows about 1110 -> 830.  Of the 480k
 // cycles at 431 rows the columns take 174k (2700 each), the update 94k, the
 // chunk loads and stores 57k and 54k, the two inverses 41k.
+//
+// FP32: the sums of (2) and, on the matrix cores, of (3) are FP64, so that a
+// value rounds once per chunk.  With FP32 sums the squared error of the first
+// solution, which the refinement's result is a power of, is 1.07 to 1.10 times
+// as large (chains of 431 to 880 products); the FP64 ones cost 0.2 to 0.3 ms of
+// the 4 to 5.4 ms of panels of a pass.
 constexpr int GF_NT = 512;
 
 // The larger of v and the v of the lane that DPP control CTRL names; a lane
@@ -342,6 +348,7 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
     constexpr int CW = (BW + NW - 1) / NW;  // substituted columns per wave
     static_assert(NB % BW == 0 && BW % KS == 0 && BW <= 16, "whole chunks, whole slabs");
     typedef T V2 __attribute__((ext_vector_type(2)));
+    typedef double D2 __attribute__((ext_vector_type(2)));
     __shared__ V2 Ts[NB][NB + 1];  // the panel's top rows as they become final (padded: column reads)
     __shared__ V2 slab[NW][2][64 * KS];
     __shared__ V2 Ux[NB][BW];
@@ -374,8 +381,8 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
     // x - l u: FP64 in two fused steps per part; FP32 with l u formed first, so
     // that a step rounds at x's size once, not twice (the refinement's last
     // error is a power of the FP32 factors')
-    auto submul = [](V2 &x, V2 l, V2 u) {
-        if constexpr (sizeof(T) == 8) {
+    auto submul = [](auto &x, auto l, auto u) {
+        if constexpr (sizeof(x.x) == 8) {
             x.x = fma(-l.x, u.x, x.x);
             x.x = fma(l.y, u.y, x.x);
             x.y = fma(-l.x, u.y, x.y);
@@ -487,22 +494,27 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
             if (rows_here(0)) fetch(0, S0{}, 0, 0);  // (3)'s first slab, beside (2)
             // (2) x_i = a_i - sum_{k<i} L_ik x_k for positions i < j0
             if (wave < bw) {
-                V2 x[CW];
+                D2 x[CW];
 #pragma unroll
-                for (int e = 0; e < CW; ++e) x[e] = lane < j0 ? Ux[lane][min(wave + NW * e, BW - 1)] : zero;
+                for (int e = 0; e < CW; ++e) {
+                    const V2 u = lane < j0 ? Ux[lane][min(wave + NW * e, BW - 1)] : zero;
+                    x[e] = D2{(double)u.x, (double)u.y};
+                }
 #pragma unroll 4
                 for (int k = 0; k < j0 - 1; ++k) {
                     const V2 l = (lane > k && lane < j0) ? Ts[lane][k] : zero;
 #pragma unroll
-                    for (int e = 0; e < CW; ++e) submul(x[e], l, V2{rlane(x[e].x, k), rlane(x[e].y, k)});
+                    for (int e = 0; e < CW; ++e)
+                        submul(x[e], D2{(double)l.x, (double)l.y}, D2{rlane(x[e].x, k), rlane(x[e].y, k)});
                 }
 #pragma unroll
                 for (int e = 0; e < CW; ++e) {
                     const int c = wave + NW * e;
                     if (lane < j0 && c < bw) {
-                        Ux[lane][c] = x[e];
-                        Ts[lane][j0 + c] = x[e];
-                        store(at(phys[lane], j0 + c), x[e]);
+                        const V2 u{(T)x[e].x, (T)x[e].y};
+                        Ux[lane][c] = u;
+                        Ts[lane][j0 + c] = u;
+                        store(at(phys[lane], j0 + c), u);
                     }
                 }
             }
@@ -515,7 +527,8 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
                     // on the matrix cores, 16 rows at a time: 16 columns as
                     // four real products per complex one, or 8 columns as the
                     // real product [Lr Li] [Ur Ui; -Ui Ur]
-                    typedef typename Mfma<T>::v4 v4;
+                    typedef Mfma<double> M;
+                    typedef M::v4 v4;
                     constexpr int NA = BW == 16 ? 2 : 1;
                     v4 d[4][NA];
 #pragma unroll
@@ -534,20 +547,20 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
                         for (int i = 0; i < 4; ++i) l[i] = slab[wave][q & 1][4 * (16 * i + l15) + (l4 ^ ((l15 >> 2) & 3))];
                         if constexpr (NA == 2) {
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].x, u.x, d[i][0]);
+                            for (int i = 0; i < 4; ++i) d[i][0] = M::op(l[i].x, u.x, d[i][0]);
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) d[i][1] = Mfma<T>::op(l[i].x, u.y, d[i][1]);
+                            for (int i = 0; i < 4; ++i) d[i][1] = M::op(l[i].x, u.y, d[i][1]);
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].y, -u.y, d[i][0]);
+                            for (int i = 0; i < 4; ++i) d[i][0] = M::op(l[i].y, -u.y, d[i][0]);
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) d[i][1] = Mfma<T>::op(l[i].y, u.x, d[i][1]);
+                            for (int i = 0; i < 4; ++i) d[i][1] = M::op(l[i].y, u.x, d[i][1]);
                         } else {
                             const bool im = (l15 & 8) != 0;
-                            const T b1 = im ? u.y : u.x, b2 = im ? u.x : -u.y;
+                            const double b1 = im ? u.y : u.x, b2 = im ? u.x : -u.y;
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].x, b1, d[i][0]);
+                            for (int i = 0; i < 4; ++i) d[i][0] = M::op(l[i].x, b1, d[i][0]);
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) d[i][0] = Mfma<T>::op(l[i].y, b2, d[i][0]);
+                            for (int i = 0; i < 4; ++i) d[i][0] = M::op(l[i].y, b2, d[i][0]);
                         }
                     }
                     // to the rows' own threads through this wave's spare slab
@@ -564,12 +577,12 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
                         for (int i = 0; i < BPP; ++i)
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
-                                const int row = 16 * i + Mfma<T>::row(lane, e);
+                                const int row = 16 * i + M::row(lane, e);
                                 if constexpr (NA == 2)
-                                    sp[row * BW + (l15 ^ (row & 15))] = V2{d[p * BPP + i][0][e], d[p * BPP + i][1][e]};
+                                    sp[row * BW + (l15 ^ (row & 15))] = V2{(T)d[p * BPP + i][0][e], (T)d[p * BPP + i][1][e]};
                                 else
                                     ((T *)sp)[2 * (row * BW + ((l15 & 7) ^ (row & 7))) + (l15 >> 3)] =
-                                        d[p * BPP + i][0][e];
+                                        (T)d[p * BPP + i][0][e];
                             }
                         __builtin_amdgcn_wave_barrier();
                         if (lane / RP == p) {

@@ -55,3 +55,22 @@ def test_substitution_rounds_once_per_panel(upper, prec):
         W = v.astype(np.complex128)
         W[B:, B:] = -(0.25 + 0.25j) * P.sum(0)
     _first_update(A, v, W, prec)
+
+
+@pytest.mark.parametrize("prec", ["FP32_IR", "BF16X_IR"])
+@pytest.mark.parametrize("n", [64, 600, 1100])
+def test_panel_update_rounds_once_per_chunk(n, prec):
+    """The last 16 columns of the first panel against its first 48: L = 1/2 on
+    rows 48 .. 63, U = (2^25, 1/2, ..., 1/2, -2^25), so that A = L U has 1/2 *
+    46 * 1/2 there.  v = A S A^T with S = 1 on those 16 columns, so W = S A^T
+    (64, 600, 1100: one, two, four rows a thread)."""
+    k = 48
+    u = np.full(k, 0.5)
+    u[0], u[-1] = 2.0 ** 25, -2.0 ** 25
+    A = np.eye(n)
+    A[k:B, :k] = 0.5
+    A[:k, k:B] = u[:, None]
+    A[k:B, k:B] += 0.5 * u.sum()
+    S = np.zeros((n, n))
+    S[range(k, B), range(k, B)] = 1.0
+    _first_update(A.astype(np.complex128), A @ S @ A.T, S @ A.T, prec)
