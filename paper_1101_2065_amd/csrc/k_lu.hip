@@ -263,8 +263,8 @@ __global__ __launch_bounds__(512) void k_getf2(int n, int kb, int w, Cx<T> *A, i
 // per wave, lane = row.
 //
 // The loads of (1) and (3) go through a slab of LDS per wave, four columns of
-// its 64 rows at a time, two slabs in turn (FP64: direct copies, FP32: through
-// registers): four neighbouring lanes read 64 contiguous bytes, where a lane
+// its 64 rows at a time, two slabs in turn (FP64 on 16-byte boundaries: direct
+// copies, else through registers): four neighbouring lanes read 64 contiguous bytes, where a lane
 // that reads along its own row touches 64 lines per load, eight times each,
 // which the 32 KB of L1 cannot hold for eight waves; and the next slab is on
 // its way while one is used.  Within a slab, row i keeps its four values in the
@@ -339,8 +339,8 @@ __device__ __forceinline__ void static_for(F &&f) {
 
 // GC, GI: the element types the pointers are declared with (global address
 // space for pointers read from a descriptor, so that they are not accessed as
-// flat memory).  FP64: A is 16-byte aligned.
-template <typename T, int R, int BW, typename GC = Cx<T>, typename GI = int32_t>
+// flat memory).  DMA: the slabs come by direct copies (FP64, A 16-byte aligned).
+template <typename T, int R, int BW, bool DMA, typename GC = Cx<T>, typename GI = int32_t>
 __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t sA, GI *ipiv, GC *Linv, GC *Uinv,
                                             int nblk, GI *swp, GI *info, const int b) {
     constexpr int NW = GF_NT / 64;
@@ -394,8 +394,8 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
     };
 
     // slab q & 1: columns [c0, c0 + 4) of this wave's rows 512 r ..; rows and
-    // columns past the panel repeat its last.  FP32: staging registers, set e
-    V2 stg[sizeof(T) == 8 ? 1 : 2][sizeof(T) == 8 ? 1 : KS];
+    // columns past the panel repeat its last.  Without DMA: staging registers, set e
+    V2 stg[DMA ? 1 : 2][DMA ? 1 : KS];
     typedef std::integral_constant<int, 0> S0;
     typedef std::integral_constant<int, 1> S1;
     auto fetch = [&](int q, auto set, int r, int c0) {
@@ -411,20 +411,20 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
         for (int t = 0; t < KS; ++t) {
             const GC *g = (const GC *)((const GB *)P + (min(r0 + 16 * t * ns, last) + c) * (uint32_t)sizeof(GC));
 #if defined(__HIP_DEVICE_COMPILE__)
-            if constexpr (sizeof(T) == 8)
+            if constexpr (DMA)
                 __builtin_amdgcn_global_load_lds((const dglobal<uint32_t> *)g,
                                                  (__attribute__((address_space(3))) uint32_t *)&slab[wave][q & 1][64 * t],
                                                  16, 0, 0);
             else
 #endif
-                stg[sizeof(T) == 8 ? 0 : e][sizeof(T) == 8 ? 0 : t] = load(g);
+                stg[DMA ? 0 : e][DMA ? 0 : t] = load(g);
         }
     };
     // slab q is there and the other one has been read (next: the fetch after
     // q's is under way and need not be waited for)
     auto land = [&](int q, auto set, bool next) {
         constexpr int e = set;
-        if constexpr (sizeof(T) == 8) {
+        if constexpr (DMA) {
 #if defined(__HIP_DEVICE_COMPILE__)
             if (next) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)" ::: "memory");
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -438,7 +438,7 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
     };
     auto slab_read = [&]() {  // the slab's values have arrived in registers
 #if defined(__HIP_DEVICE_COMPILE__)
-        if constexpr (sizeof(T) == 8) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (DMA) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #endif
     };
     const int swz = (lane >> 2) & 3;
@@ -792,10 +792,10 @@ __device__ __forceinline__ void getf2r_body(int n, int kb, int w, GC *A, int64_t
     for (int q = 0; q < CPW; ++q) store(Uinv + lane * NB + c0 + q, x[q]);
 }
 
-template <typename T, int R, int BW>
+template <typename T, int R, int BW, bool DMA>
 __global__ __launch_bounds__(GF_NT) void k_getf2r(int n, int kb, int w, Cx<T> *A, int64_t sA, int32_t *ipiv,
                                                   Cx<T> *Linv, Cx<T> *Uinv, int nblk, int32_t *swp, int32_t *info) {
-    getf2r_body<T, R, BW>(n, kb, w, A, sA, ipiv, Linv, Uinv, nblk, swp, info, blockIdx.x);
+    getf2r_body<T, R, BW, DMA>(n, kb, w, A, sA, ipiv, Linv, Uinv, nblk, swp, info, blockIdx.x);
 }
 
 // The index of the item whose workgroups wg0 .. include g (items ordered by wg0).
@@ -811,12 +811,12 @@ __device__ inline int group_item(const PanelItem *__restrict__ it, int n_items, 
 
 // Many batched panel factorisations in one launch (the batched driver's lock
 // steps): workgroup g factorises batch entry g - wg0 of its item.
-template <typename T, int R, int BW>
+template <typename T, int R, int BW, bool DMA>
 __global__ __launch_bounds__(GF_NT) void k_getf2r_group(const PanelItem *__restrict__ items, int n_items) {
     const PanelItem p = items[group_item(items, n_items, blockIdx.x)];
     typedef dglobal<Cx<T>> GC;
     typedef dglobal<int32_t> GI;
-    getf2r_body<T, R, BW, GC, GI>(p.n, p.kb, p.w, (GC *)p.A, p.sA, (GI *)p.ipiv, (GC *)p.Linv, (GC *)p.Uinv, p.nblk,
+    getf2r_body<T, R, BW, DMA, GC, GI>(p.n, p.kb, p.w, (GC *)p.A, p.sA, (GI *)p.ipiv, (GC *)p.Linv, (GC *)p.Uinv, p.nblk,
                                   (GI *)p.swp, (GI *)p.info, (int)(blockIdx.x - p.wg0));
 }
 
@@ -1068,6 +1068,22 @@ inline hipError_t block_solve_t(hipStream_t st, bool upper, int wo, int n, const
 // applying them all before the block's triangular solve).
 constexpr int NBO = 256;
 
+// The register panel of m <= 4096 rows: rows per thread and chunk width by m.
+template <typename T, bool DMA>
+hipError_t launch_getf2r(hipStream_t st, int m, int batch, int n, int kb, int w, Cx<T> *A, int64_t sA, int32_t *ipiv,
+                         Cx<T> *Linv, Cx<T> *Uinv, int nblk, int32_t *swp, int32_t *info) {
+#define GW_PANEL(R, BW)                                                                                            \
+    hipLaunchKernelGGL((k_getf2r<T, R, BW, DMA>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,    \
+                       Uinv, nblk, swp, info)
+    if (m <= 512) GW_PANEL(1, 16);
+    else if (m <= 1024) GW_PANEL(2, 16);
+    else if (m <= 2048) GW_PANEL(4, 8);
+    else if (m <= 3072) GW_PANEL(6, 4);
+    else GW_PANEL(8, 4);
+#undef GW_PANEL
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv, Cx<T> *Linv, Cx<T> *Uinv,
                       Cx<T> *scratch, int32_t *info, int batch) {
@@ -1076,15 +1092,18 @@ hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv
     int32_t *swp = (int32_t *)(scratch + (int64_t)batch * NB * n);
     hipError_t e;
     OpRecorder *rec = g_rec;
-    // the register panels copy FP64 values straight to LDS, 16 bytes each
-    const bool al = sizeof(T) == 4 || ((uintptr_t)A & 15) == 0;
+    // the register panels' direct copies take 16 bytes at a time; from rows that
+    // do not lie so (FP64), and in FP32, they stage through registers (a solve
+    // from A on 8-byte boundaries, 1100 products and 128 points: 20.8 ms, 17.6
+    // on 16-byte ones, 37.9 by the panel in memory)
+    const bool dma = sizeof(T) == 8 && ((uintptr_t)A & 15) == 0;
     if (rec) rec->mark();
     for (int KB = 0; KB < n; KB += NBO) {
         const int WO = min(NBO, n - KB);
         for (int kb = KB; kb < KB + WO; kb += NB) {
             const int w = min(NB, n - kb);
             const int m = n - kb;
-            const bool regs = al && m <= 4096;
+            const bool regs = m <= 4096;
             if (rec) {
                 // lock-step recording: the panel (a grouped launch per
                 // register-row variant) and its row exchanges
@@ -1092,7 +1111,8 @@ hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv
                 o.p = PanelItem{A, sA, ipiv, swp, info, Linv, Uinv, n, kb, w, nblk, batch, 0};
                 if (regs) {
                     o.kind = RecOp::PANEL;
-                    o.key = (m <= 512 ? 0 : m <= 1024 ? 1 : m <= 2048 ? 2 : m <= 3072 ? 3 : 4) + (sizeof(T) == 4 ? 5 : 0);
+                    o.key = (m <= 512 ? 0 : m <= 1024 ? 1 : m <= 2048 ? 2 : m <= 3072 ? 3 : 4) +
+                            (sizeof(T) == 4 ? 5 : dma ? 0 : 10);
                     rec->ops.push_back(o);
                 } else {
                     rec->other([=](hipStream_t s2) {
@@ -1113,21 +1133,10 @@ hipError_t getrf_impl(hipStream_t st, int n, Cx<T> *A, int64_t sA, int32_t *ipiv
             if (!regs)
                 hipLaunchKernelGGL(k_getf2<T>, dim3(batch), dim3(512), 0, st, n, kb, w, A, sA, ipiv, Linv, Uinv, nblk,
                                    scratch, swp, info);
-            else if (m <= 512)
-                hipLaunchKernelGGL((k_getf2r<T, 1, 16>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
-                                   Uinv, nblk, swp, info);
-            else if (m <= 1024)
-                hipLaunchKernelGGL((k_getf2r<T, 2, 16>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
-                                   Uinv, nblk, swp, info);
-            else if (m <= 2048)
-                hipLaunchKernelGGL((k_getf2r<T, 4, 8>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
-                                   Uinv, nblk, swp, info);
-            else if (m <= 3072)
-                hipLaunchKernelGGL((k_getf2r<T, 6, 4>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
-                                   Uinv, nblk, swp, info);
+            else if (dma)
+                (void)launch_getf2r<T, sizeof(T) == 8>(st, m, batch, n, kb, w, A, sA, ipiv, Linv, Uinv, nblk, swp, info);
             else
-                hipLaunchKernelGGL((k_getf2r<T, 8, 4>), dim3(batch), dim3(GF_NT), 0, st, n, kb, w, A, sA, ipiv, Linv,
-                                   Uinv, nblk, swp, info);
+                (void)launch_getf2r<T, false>(st, m, batch, n, kb, w, A, sA, ipiv, Linv, Uinv, nblk, swp, info);
             if ((e = hipGetLastError()) != hipSuccess) return e;
             if (n - w > 0) {
                 ProfScope pl(st, "laswp", 0.0, 2.0 * w * (n - w) * sizeof(Cx<T>) * (double)batch);
@@ -1356,23 +1365,27 @@ hipError_t launch_c2z_set(hipStream_t st, const zflt *d, zdbl *W, int64_t n_per,
 }
 
 // Panel keys: (R, BW) = (1, 16), (2, 16), (4, 8), (6, 4), (8, 4) for panels of at
-// most 512, 1024, 2048, 3072, 4096 rows, complex double; +5 complex float.
+// most 512, 1024, 2048, 3072, 4096 rows, complex double; +5 complex float, +10
+// complex double off 16-byte boundaries.
 hipError_t launch_panel_group(hipStream_t st, int key, const PanelItem *items, int n_items, int64_t n_wg) {
     if (n_items <= 0 || n_wg <= 0) return hipSuccess;
-    if (key < 0 || key > 9 || n_wg > INT32_MAX) return hipErrorInvalidValue;
+    if (key < 0 || key > 14 || n_wg > INT32_MAX) return hipErrorInvalidValue;
     const dim3 grid((unsigned)n_wg), blk(GF_NT);
-    switch (key) {
-        case 0: hipLaunchKernelGGL((k_getf2r_group<double, 1, 16>), grid, blk, 0, st, items, n_items); break;
-        case 1: hipLaunchKernelGGL((k_getf2r_group<double, 2, 16>), grid, blk, 0, st, items, n_items); break;
-        case 2: hipLaunchKernelGGL((k_getf2r_group<double, 4, 8>), grid, blk, 0, st, items, n_items); break;
-        case 3: hipLaunchKernelGGL((k_getf2r_group<double, 6, 4>), grid, blk, 0, st, items, n_items); break;
-        case 4: hipLaunchKernelGGL((k_getf2r_group<double, 8, 4>), grid, blk, 0, st, items, n_items); break;
-        case 5: hipLaunchKernelGGL((k_getf2r_group<float, 1, 16>), grid, blk, 0, st, items, n_items); break;
-        case 6: hipLaunchKernelGGL((k_getf2r_group<float, 2, 16>), grid, blk, 0, st, items, n_items); break;
-        case 7: hipLaunchKernelGGL((k_getf2r_group<float, 4, 8>), grid, blk, 0, st, items, n_items); break;
-        case 8: hipLaunchKernelGGL((k_getf2r_group<float, 6, 4>), grid, blk, 0, st, items, n_items); break;
-        default: hipLaunchKernelGGL((k_getf2r_group<float, 8, 4>), grid, blk, 0, st, items, n_items); break;
+#define GW_PANEL(T, R, BW, DMA) \
+    hipLaunchKernelGGL((k_getf2r_group<T, R, BW, DMA>), grid, blk, 0, st, items, n_items)
+#define GW_PANELS(T, DMA)                     \
+    switch (key % 5) {                        \
+        case 0: GW_PANEL(T, 1, 16, DMA); break; \
+        case 1: GW_PANEL(T, 2, 16, DMA); break; \
+        case 2: GW_PANEL(T, 4, 8, DMA); break;  \
+        case 3: GW_PANEL(T, 6, 4, DMA); break;  \
+        default: GW_PANEL(T, 8, 4, DMA); break; \
     }
+    if (key < 5) GW_PANELS(double, true)
+    else if (key < 10) GW_PANELS(float, false)
+    else GW_PANELS(double, false)
+#undef GW_PANELS
+#undef GW_PANEL
     return hipGetLastError();
 }
 
