@@ -47,7 +47,7 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
     constexpr int ea = AC ? 2 : 1, eb = BC ? 2 : 1, ec = CC ? 2 : 1;
     constexpr int EA = BM * BK / 256, TPRA = BK / EA;  // elements per thread, threads per row (A)
     constexpr int EB = BK * BN / 256, TPRB = BN / EB;  // (B)
-    static_assert(EA >= 1 && EB >= 1 && TPRA >= 1 && TPRB >= 1, "tile too small");
+    static_assert(EA >= 1 && EB >= 1 && TPRA >= 1 && TPRB >= 1 && BK % 8 == 0, "tile too small");
     typedef typename Mfma<T>::v4 v4;
     // in the Cauchy product's tile (MIR) the transposed A rows are padded by
     // one value: unpadded, the K rows of the tile are a multiple of the LDS
@@ -156,7 +156,9 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
         if (more) gload(k0 + BK);
 #pragma unroll
         for (int kk = 0; kk < BK; kk += 4) {
-            const int kl = kk + (lane >> 4);
+            // a real A: k = 0 2 4 6, then 1 3 5 7 of each 8, as in rgemm_tile, so
+            // that a product's bits do not tell which of the two formed it
+            const int kl = AC ? kk + (lane >> 4) : (kk & ~7) + 2 * (lane >> 4) + ((kk >> 2) & 1);
             T ar[WM], ai[WM], br[WN], bi[WN];
 #pragma unroll
             for (int i = 0; i < WM; ++i) {
