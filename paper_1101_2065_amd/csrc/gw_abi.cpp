@@ -501,13 +501,12 @@ gw_status a_route_ws(gw_ctx *c, const std::string &pre, int n, int nhb, int n_om
     gw_status s;
     if ((s = ws(c, pre + "aD", 8 * dd * w->dchunk, &q)) != GW_OK) return s;
     w->D = (double *)q;
-    if ((s = ws(c, pre + "aB", 8 * (size_t)w->xs * std::max(1, nhb), &q)) != GW_OK) return s;
-    w->B = (double *)q;
-    w->V = nullptr;
-    if (n & 1) {
-        if ((s = ws(c, pre + "aV", 8 * dd, &q)) != GW_OK) return s;
-        w->V = (double *)q;
-    }
+    // v's padded rows lie in bin 0 of B, into which the identity only goes after
+    // the products, and the `lead` values before it (an even number of them)
+    const size_t lead = n & 1 ? (dd - (size_t)w->xs + 1) & ~(size_t)1 : 0;
+    if ((s = ws(c, pre + "aB", 8 * (lead + (size_t)w->xs * std::max(1, nhb)), &q)) != GW_OK) return s;
+    w->B = (double *)q + lead;
+    w->V = n & 1 ? (double *)q : nullptr;
     if ((s = ws(c, pre + "aT", 16 * (size_t)(n_omega / 2 + 1) * std::max(1, nhb), &q)) != GW_OK) return s;
     w->T = (zdbl *)q;
     return GW_OK;

@@ -72,7 +72,7 @@ gw_status build_enqueue(gw_ctx *c, const BuildPlan &p, hipStream_t st, void *chi
 // bins) and the Cauchy-transform matrix T of the solved half of the mesh.
 // Rows are padded to an even number of values (ldd per row of D, xs per bin of
 // B), which the products' 16-byte copies need; V: room for v with rows of ldd
-// values, null for an even n.
+// values (it holds bin 0 of B until that is formed), null for an even n.
 struct ARouteWs {
     double *D = nullptr, *B = nullptr, *V = nullptr;
     zdbl *T = nullptr;
