@@ -57,27 +57,28 @@ namespace {
 // ------------------------------------------------------------------ autotuner
 // Table: (precision, size class) -> tile of the long complex products of the
 // LU and the solves (0: 64x64, 1: 128x64, 2: 64x32, 3: 32x32 in FP64, 128x32 in
-// FP32).  FP64 entries are kept under the name of the direct-to-LDS kernels,
-// so that a table measured with other kernels is not read for them.
+// FP32).  A measurement made otherwise, with other kernels (FP64) or on zeros and
+// four frequencies (FP32: see below), stands under another name and is not read.
 // The size class is n rounded up to a multiple of 256; the precision is that
 // of the factorisation (FP64, or FP32 for both mixed forms: under BF16x the
 // rank-K trailing updates run on the split-BF16 kernel, and the FP32 table
 // entry serves its remaining complex-float products).  A class is measured the
 // first time it is seen, on the molecule's own first trailing update
-// (M = N = n - 256, K = 256, as many frequencies as a factorisation batch holds
-// within 1 GiB: with four, a launch too small to fill the GPU made the smallest
-// tiles look best): one warm-up launch and five timed ones per tile, the median
-// kept.  The table lives in
+// (M = N = n - 256, K = 256, as many frequencies as its factorisation batch
+// holds, within 1 GiB: with four, a launch too small to fill the GPU made the
+// smallest tiles look best): one warm-up launch and five timed ones per tile,
+// the median kept.  The operands' memory is given back.  The table lives in
 // memory and in a JSON file ($GW_TUNE_FILE, default $HOME/.cache/gw_tune.json).
 std::mutex g_tune_mu;
 std::map<std::string, int> g_tune;
 bool g_tune_loaded = false;
 
 std::string tune_key(int cls, gw_precision prec) {
-    return std::string(prec == GW_FP64 ? "zgemm_lds_fp64" : "cgemm_fp32") + "_n" + std::to_string(cls);
+    return std::string(prec == GW_FP64 ? "zgemm_lds_fp64" : "cgemm_full_fp32") + "_n" + std::to_string(cls);
 }
 
-gw_status tune_tile(gw_ctx *ctx, int n, gw_precision prec, hipStream_t st, int *tile) {
+// n_omega, budget: the mesh and the workspace budget of the molecule's solve.
+gw_status tune_tile(gw_ctx *ctx, int n, int n_omega, gw_precision prec, size_t budget, hipStream_t st, int *tile) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     const std::string path = gwt::cache_path();
     if (!g_tune_loaded) {
@@ -100,12 +101,17 @@ gw_status tune_tile(gw_ctx *ctx, int n, gw_precision prec, hipStream_t st, int *
     const bool dbl = prec == GW_FP64;
     const int M = n - 256, K = 256;
     const size_t esz = dbl ? 16 : 8;
-    // as many frequencies as the factorisation's batches hold, within 1 GiB
-    const int batch = (int)std::max<size_t>(4, std::min<size_t>(256, ((size_t)1 << 30) / (((size_t)M * M + 2 * (size_t)M * K) * esz)));
+    const size_t per = ((size_t)M * M + 2 * (size_t)M * K) * esz;
+    const int batch = (int)std::max<size_t>(
+        1, std::min<size_t>(gwp::solve_batch_max(n, n_omega, !dbl, budget), ((size_t)1 << 30) / per));
     const size_t elems = (size_t)batch * ((size_t)M * M + 2 * (size_t)M * K);
     void *buf;
     gw_status s = gwp::ws(ctx, "tune", elems * esz, &buf);
     if (s != GW_OK) return s;
+    struct Release {
+        gw_ctx *c;
+        ~Release() { gwp::ws_release(c, "tune"); }
+    } release{ctx};
     GW_HIP(ctx, gwk::launch_fill_test(st, (uint32_t *)buf, (int64_t)(elems * esz / 4), dbl));
     hipEvent_t e0, e1;
     GW_HIP(ctx, hipEventCreate(&e0));
@@ -373,7 +379,7 @@ gw_status gw_batch_create(gw_ctx *ctx, int32_t n_mol, const gw_molecule *mols, c
         if (s != GW_OK) return bail(s);
         b->norms.push_back((double *)p);
         int tile = 0;
-        s = tune_tile(ctx, mols[i].n_prod, prec, st, &tile);
+        s = tune_tile(ctx, mols[i].n_prod, g->n_omega, prec, ctx->budget / (b->mode != 0 ? n_mol : nbr), st, &tile);
         if (s != GW_OK) return bail(s);
         b->tile.push_back(tile);
     }
