@@ -239,7 +239,7 @@ int solve_batch_max(int n, int n_omega, bool mixed, size_t budget) {
     const size_t pf = per_freq_bytes(n, mixed);
     const size_t cap = std::min<size_t>(budget / 2, (size_t)24 << 30);
     int nb = (int)std::max<size_t>(1, std::min<size_t>(cap / pf, 256));
-    return std::max(1, std::min(nb, n_omega / 2));
+    return std::max(1, std::min(nb, n_omega == 2 ? 2 : n_omega / 2));
 }
 
 // A = 1 - v chi0 for nb frequencies.  The rows of v are padded to an even number
@@ -361,10 +361,11 @@ gw_status solve_batch_mixed(gw_ctx *c, hipStream_t st, int n, const double *v, i
     return GW_OK;
 }
 
-// frequency batches: {0}, then [n/2, n) in equal chunks of at most nbmax
+// frequency batches: {0}, then [n/2, n) in equal chunks of at most nbmax (of two
+// points, -omega_max and 0, neither mirrors the other)
 std::vector<std::pair<int, int>> freq_batches(int n_omega, int nbmax) {
     std::vector<std::pair<int, int>> b;
-    if (n_omega == 2) return {{0, 2}};
+    if (n_omega == 2 && nbmax >= 2) return {{0, 2}};
     b.push_back({0, 1});
     const int cnt = n_omega / 2, nbat = (cnt + nbmax - 1) / nbmax;
     for (int i = 0, j = n_omega / 2; i < nbat; ++i) {
@@ -1359,7 +1360,7 @@ gw_status solve_W_impl(gw_ctx *ctx, const double *v, int32_t v_is_diag, int32_t 
             // so it runs on the context's second stream beside the batches
             bool side = !ctx->own_stream && n_omega >= 8;
             gwp::SolvePlan p0;
-            if (side && (s = gwp::solve_plan(ctx, n, 2, false, "j0", &p0)) != GW_OK) {
+            if (side && (s = gwp::solve_plan(ctx, n, 1, false, "j0", &p0)) != GW_OK) {
                 if (s != GW_E_OOM) return s;
                 side = false;  // no room for a second workspace: j = 0 stays in order
             }
@@ -1418,7 +1419,7 @@ gw_status solve_W_impl(gw_ctx *ctx, const double *v, int32_t v_is_diag, int32_t 
                     // A of the batch (chi0 may already be overwritten in place)
                     ++n_fallback;
                     gwp::SolvePlan p64;
-                    if ((s = gwp::solve_plan(ctx, n, 2, false, "fb", &p64)) != GW_OK) return s;
+                    if ((s = gwp::solve_plan(ctx, n, 1, false, "fb", &p64)) != GW_OK) return s;
                     GW_HIP(ctx, hipMemcpyAsync(p64.w.A, wb.A + (int64_t)b * nn, (size_t)nn * 16,
                                                hipMemcpyDeviceToDevice, st));
                     s = gwp::solve_batch_fp64(ctx, st, n, v, v_is_diag, nullptr, W + (j0 + b) * nn, 1, p64.w);

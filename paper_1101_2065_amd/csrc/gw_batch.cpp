@@ -440,7 +440,7 @@ gw_status gw_batch_run(gw_batch *b, void *stream, gw_report *reps) {
                     continue;
                 }
                 if (!planned) {
-                    gw_status s = gwp::solve_plan(ctx, b->n[i], 2, false, "bfb", &p64);
+                    gw_status s = gwp::solve_plan(ctx, b->n[i], 1, false, "bfb", &p64);
                     if (s != GW_OK) return s;
                     planned = true;
                 }
