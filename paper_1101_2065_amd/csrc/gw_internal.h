@@ -157,8 +157,8 @@ hipError_t launch_fill_u64(hipStream_t st, uint64_t *p, int64_t n, uint64_t valu
 // lone point j = 0.
 hipError_t launch_cauchy_A(hipStream_t st, int n, int n_omega, int nhb, int j0, double domega, double eps,
                            double *X, int64_t xs, zdbl *T, zdbl *A);
-hipError_t launch_zdgemm_wide(hipStream_t st, int M, int N, int K, double alpha, const zdbl *A, int64_t lda,
-                              const double *B, int64_t ldb, zdbl *C, int64_t ldc, bool mirror);
+hipError_t launch_zdgemm_mirror(hipStream_t st, int M, int N, int K, double alpha, const zdbl *A, int64_t lda,
+                                const double *B, int64_t ldb, zdbl *C, int64_t ldc);
 hipError_t launch_fill_u32(hipStream_t st, uint32_t *p, int64_t n, uint32_t value);
 
 // Exact int64 histogram H[nhb][n_upper] (Section 5.A eq. chi_by_spectra).

@@ -698,8 +698,8 @@ hipError_t launch_cauchy_A(hipStream_t st, int n, int n_omega, int nhb, int j0, 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     // the solved half j = n_omega/2 .. n_omega-1 in one product, which also
     // writes the other half by A(-omega) = A(omega)* (v real)
-    if ((e = launch_zdgemm_wide(st, half, (int)nn, nhb, -1.0, T + nhb, nhb, X, xs, A + (int64_t)half * nn, nn,
-                                true)) != hipSuccess)
+    if ((e = launch_zdgemm_mirror(st, half, (int)nn, nhb, -1.0, T + nhb, nhb, X, xs, A + (int64_t)half * nn, nn)) !=
+        hipSuccess)
         return e;
     {
         ProfScope ps(st, "cauchy_row0", 4.0 * (double)nn * nhb, 8.0 * (double)nn * nhb + 16.0 * (double)nn);

@@ -7,13 +7,14 @@
 // solves use three real MFMA products per complex product, ac, bd and
 // (a + b)(c + d) (a quarter less matrix-core work, normwise as accurate); the
 // FP64 refinement residual and the FP32 products use four.
-// Tiles: 256-thread workgroups, four 64-wide waves in 2x2.  The complex FP64
-// products (zgemm_tile) copy their operands from global memory straight into
-// LDS in matrix-core order and keep almost nothing but MFMA instructions in
-// the K loop; the real-times-complex, real and FP32 products (gemm_tile) stage
-// them through registers: 64x64 (K steps of 16) and 128x64 (K steps of 8) at
-// two waves per SIMD, and narrow FP32 tiles.  The tiles are dealt to the XCDs
-// in contiguous ranges (each XCD has its own L2).
+// Tiles: 256-thread workgroups, four 64-wide waves in 2x2.  The FP64 products,
+// complex (zgemm_tile), real and real-times-complex (rgemm_tile), copy their
+// operands from global memory straight into LDS in matrix-core order and keep
+// almost nothing but MFMA instructions in the K loop.  The FP32 products
+// (gemm_tile) stage them through registers, 64x64 (K steps of 16), 128x64 and
+// narrower (K steps of 8), as do at 64x64 the real and real-times-complex ones
+// whose rows rgemm_tile cannot copy 16 bytes at a time.  The tiles are dealt to
+// the XCDs in contiguous ranges (each XCD has its own L2).
 #include "gw_internal.h"
 #include "gw_prof.h"
 #include "k_mfma.h"
@@ -34,10 +35,7 @@ namespace {
 // LDS stage.
 // One (32 WM) x (32 WN) tile of C with its top-left corner at (m0, n0); A, B,
 // C (and C32) point at the tile's batch entry.
-// MIR: row r >= 1 of C is also written, conjugated, r rows before C's first
-// row (C(-omega) = C(omega)* for a C whose rows are omega_r on a symmetric
-// mesh starting at omega = 0).
-template <typename T, bool AC, bool BC, int WM, int WN, int BK, typename GT = T, bool MIR = false>
+template <typename T, bool AC, bool BC, int WM, int WN, int BK, typename GT = T>
 __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT *__restrict__ A, int64_t lda,
                                           const GT *B, int64_t ldb, T beta, GT *C, int64_t ldc, int add_eye,
                                           float *C32, int m0, int n0) {
@@ -49,19 +47,13 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
     constexpr int EB = BK * BN / 256, TPRB = BN / EB;  // (B)
     static_assert(EA >= 1 && EB >= 1 && TPRA >= 1 && TPRB >= 1 && BK % 8 == 0, "tile too small");
     typedef typename Mfma<T>::v4 v4;
-    // in the Cauchy product's tile (MIR) the transposed A rows are padded by
-    // one value: unpadded, the K rows of the tile are a multiple of the LDS
-    // bank span apart, so the stores of a wave (several K rows of few tile
-    // rows) pile onto the same banks (10% more bank-conflict cycles, 3%
-    // slower).  The other tiles run faster unpadded.  The 64x64 tile also
-    // gives each thread B columns TPRB apart.
-    constexpr int PA = MIR ? 1 : 0;
+    // the 64x64 tile gives each thread B columns TPRB apart
     constexpr int SB = (BK == 16) ? TPRB : 1;
     // complex operands are staged interleaved {re, im}: one 16-byte LDS read
     // per operand value instead of two 8-byte ones
     typedef T T2 __attribute__((ext_vector_type(2)));
-    __shared__ T Ar[2][AC ? 1 : BK][AC ? 1 : BM + PA];
-    __shared__ T2 Ac[2][AC ? BK : 1][AC ? BM + PA : 1];
+    __shared__ T Ar[2][AC ? 1 : BK][AC ? 1 : BM];
+    __shared__ T2 Ac[2][AC ? BK : 1][AC ? BM : 1];
     __shared__ T Br[2][BC ? 1 : BK][BC ? 1 : BN];
     __shared__ T2 Bc[2][BC ? BK : 1][BC ? BN : 1];
 
@@ -227,13 +219,6 @@ __device__ __forceinline__ void gemm_tile(int M, int N, int K, T alpha, const GT
                     if (add_eye && row == col) vr += T(1);
                     pc[0] = vr;
                     if constexpr (CC) pc[1] = vi;
-                    if constexpr (MIR) {
-                        if (row >= 1) {
-                            GT *pm = C + (col - (int64_t)row * ldc) * ec;
-                            pm[0] = vr;
-                            pm[1] = -vi;
-                        }
-                    }
                     if (C32) {
                         float *q = C32 + ((int64_t)row * ldc + col) * 2;
                         q[0] = (float)vr;
@@ -701,37 +686,30 @@ bool rgemm_ok(int N, const void *A, int64_t lda, int64_t sA, bool ac, const void
     return (((uintptr_t)A | (uintptr_t)B) & 15) == 0 && a_even && ((ldb | sB) & 1) == 0 && ((N & 1) == 0 || ldb > N);
 }
 
-// XR: tile order.  0: as launched; 1 and 2: workgroups are dealt to the
-// eight XCDs in turn, each with its own L2, so each XCD gets a contiguous
-// range of tiles, row band by row band (1: tiles sharing an A row band share
-// that XCD's L2) or column band by column band (2: tiles sharing a B column
-// band do, for products whose B is much larger than A).
-template <typename T, bool AC, bool BC, int WM, int WN, int BK, int OCC, int XR, bool MIR = false>
+// XR: workgroups are dealt to the eight XCDs in turn, each with its own L2, so
+// each XCD gets a contiguous range of tiles, row band by row band (tiles sharing
+// an A row band share that XCD's L2); else the tiles as launched.
+template <typename T, bool AC, bool BC, int WM, int WN, int BK, int OCC, bool XR>
 __global__ __launch_bounds__(256, OCC) void k_gemm(int M, int N, int K, T alpha, const T *__restrict__ A, int64_t lda,
                                                  int64_t sA, const T *B, int64_t ldb, int64_t sB, T beta,
                                                  T *C, int64_t ldc, int64_t sC, int add_eye, float *C32,
                                                  int64_t sC32) {
     constexpr int ea = AC ? 2 : 1, eb = BC ? 2 : 1, ec = (AC || BC) ? 2 : 1;
     int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-    if constexpr (XR != 0) {
+    if constexpr (XR) {
         const int gx = gridDim.x, gy = gridDim.y;
         const int64_t nt = (int64_t)gx * gy * gridDim.z, l = bx + (int64_t)gx * (by + (int64_t)gy * bz);
         const int64_t n8 = nt / 8, t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;
-        if constexpr (XR == 1) {
-            bx = (int)(t % gx);
-            by = (int)((t / gx) % gy);
-        } else {
-            by = (int)(t % gy);
-            bx = (int)((t / gy) % gx);
-        }
+        bx = (int)(t % gx);
+        by = (int)((t / gx) % gy);
         bz = (int)(t / ((int64_t)gx * gy));
     }
     A += (int64_t)bz * sA * ea;
     B += (int64_t)bz * sB * eb;
     C += (int64_t)bz * sC * ec;
     if (C32) C32 += (int64_t)bz * sC32 * 2;
-    gemm_tile<T, AC, BC, WM, WN, BK, T, MIR>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, add_eye, C32, by * 32 * WM,
-                                             bx * 32 * WN);
+    gemm_tile<T, AC, BC, WM, WN, BK>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, add_eye, C32, by * 32 * WM,
+                                     bx * 32 * WN);
 }
 
 // Tile t of a multi-product launch: its item (searched from item a up; the
@@ -1217,35 +1195,19 @@ hipError_t launch_zgemm_lu(hipStream_t st, int M, int N, int K, double alpha, co
 // C = alpha A B (beta = 0) for complex A (M x K, small) times real B (K x N,
 // N large), tiles ordered column band by column band so each slice of B is
 // read from HBM once: the Cauchy transform of the spectral bins on the
-// A route (M frequencies, N matrix entries, K bins).  mirror: row r >= 1 is
-// also written, conjugated, at row -r (C's rows are the mesh points from
-// omega = 0 up; the rows before C are those of -omega).
-hipError_t launch_zdgemm_wide(hipStream_t st, int M, int N, int K, double alpha, const zdbl *A, int64_t lda,
-                              const double *B, int64_t ldb, zdbl *C, int64_t ldc, bool mirror) {
+// A route (M frequencies, N matrix entries, K bins).  Row r >= 1 is also
+// written, conjugated, at row -r (C's rows are the mesh points from omega = 0
+// up; the rows before C are those of -omega).  B's rows are the caller's own,
+// laid out for 16-byte copies.
+hipError_t launch_zdgemm_mirror(hipStream_t st, int M, int N, int K, double alpha, const zdbl *A, int64_t lda,
+                                const double *B, int64_t ldb, zdbl *C, int64_t ldc) {
     if (M <= 0 || N <= 0) return hipSuccess;
-    ProfScope ps(st, "cauchy_gemm", 4.0 * M * (double)N * K,
-                 8.0 * (double)K * N + 16.0 * (double)(mirror ? 2 * M - 1 : M) * N);
-    const double *A_ = (const double *)A;
-    double *C_ = (double *)C;
+    if (!rgemm_ok(N, A, lda, 0, true, B, ldb, 0)) return hipErrorInvalidValue;
+    ProfScope ps(st, "cauchy_gemm", 4.0 * M * (double)N * K, 8.0 * (double)K * N + 16.0 * (double)(2 * M - 1) * N);
     const int64_t z = 0;
-    float *none = nullptr;
-    if (rgemm_ok(N, A, lda, 0, true, B, ldb, 0)) {
-        const dim3 grid((N + 63) / 64, (M + 127) / 128, 1);
-        if (mirror)
-            hipLaunchKernelGGL((k_rgemm<true, 4, 2, 8, 2, true, true>), grid, dim3(256), 0, st, M, N, K, alpha, A_, lda,
-                               z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
-        else
-            hipLaunchKernelGGL((k_rgemm<true, 4, 2, 8, 2, true, false>), grid, dim3(256), 0, st, M, N, K, alpha, A_,
-                               lda, z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
-        return hipGetLastError();
-    }
-    const dim3 grid((N + 63) / 64, (M + 63) / 64, 1);
-    if (mirror)
-        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2, true>), grid, dim3(256), 0, st, M, N, K, alpha,
-                           A_, lda, z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
-    else
-        hipLaunchKernelGGL((k_gemm<double, true, false, 2, 2, 16, 2, 2>), grid, dim3(256), 0, st, M, N, K, alpha, A_,
-                           lda, z, B, ldb, z, 0.0, C_, ldc, z, 0, none, z);
+    hipLaunchKernelGGL((k_rgemm<true, 4, 2, 8, 2, true, true>), dim3((N + 63) / 64, (M + 127) / 128, 1), dim3(256), 0,
+                       st, M, N, K, alpha, (const double *)A, lda, z, B, ldb, z, 0.0, (double *)C, ldc, z, 0,
+                       (float *)nullptr, z);
     return hipGetLastError();
 }
 
