@@ -37,17 +37,22 @@ namespace {
 
 constexpr int TNB = 64;  // panel
 
+// v2: a complex value in registers and LDS; G2: in global memory, where it lies
+// on its real type's boundaries.  (Functions take T and name G2 themselves: a
+// type given as a template argument loses its alignment.)
 template <typename T>
 struct Tv;
 template <>
 struct Tv<double> {
     typedef double v2 __attribute__((ext_vector_type(2)));
     typedef double v2u __attribute__((ext_vector_type(2), aligned(8)));
+    typedef dglobal<v2u> G2;
 };
 template <>
 struct Tv<float> {
     typedef float v2 __attribute__((ext_vector_type(2)));
     typedef float v2u __attribute__((ext_vector_type(2), aligned(4)));
+    typedef dglobal<v2u> G2;
 };
 typedef Tv<double>::v2 zd2;
 typedef Mfma<double>::v4 v4;
@@ -61,19 +66,21 @@ struct Acc {
     __device__ __forceinline__ double re(int h, int e) const { return r[h][e] - i[h][e]; }
     __device__ __forceinline__ double im(int h, int e) const { return s[h][e] - r[h][e] - i[h][e]; }
 };
-template <typename V2, typename G2>
-__device__ __forceinline__ void load4(V2 (&a)[4], const G2 *row, int k0, int lk, int kmax) {
+template <typename T>
+__device__ __forceinline__ void load4(typename Tv<T>::v2 (&a)[4], const typename Tv<T>::G2 *row, int k0, int lk,
+                                      int kmax) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) a[q] = row[min(k0 + 4 * q + lk, kmax)];
 }
-template <typename G2, typename V2>
-__device__ __forceinline__ void mul64(Acc &c, V2 (&a)[4], const G2 *row, int lk, int lane, int kmax, const zd2 *b) {
+template <typename T>
+__device__ __forceinline__ void mul64(Acc &c, typename Tv<T>::v2 (&a)[4], const typename Tv<T>::G2 *row, int lk,
+                                      int lane, int kmax, const zd2 *b) {
 #pragma unroll
     for (int j = 0; j < NH; ++j) c.r[j] = c.i[j] = c.s[j] = v4{0, 0, 0, 0};
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
-        V2 n[4];
-        if (h < 3) load4(n, row, 16 * (h + 1), lk, kmax);
+        typename Tv<T>::v2 n[4];
+        if (h < 3) load4<T>(n, row, 16 * (h + 1), lk, kmax);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             zd2 bv[NH];
@@ -100,10 +107,12 @@ __device__ __forceinline__ void mul64(Acc &c, V2 (&a)[4], const G2 *row, int lk,
 // (upper only): the block's first row's index among X's columns; panel p is
 // then needed in columns below tri + 64 (p + 1) alone (a symmetric result, its
 // lower triangle).
-template <typename T, bool UPPER, typename G2>
-__device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t ldt, const G2 *inv, G2 *X, int64_t ldx,
-                                            int tri, int c0) {
+template <typename T, bool UPPER>
+__device__ __forceinline__ void solve_strip(int wo, int n, const typename Tv<T>::G2 *Tm, int64_t ldt,
+                                            const typename Tv<T>::G2 *inv, typename Tv<T>::G2 *X, int64_t ldx, int tri,
+                                            int c0) {
     typedef typename Tv<T>::v2 V2;
+    typedef typename Tv<T>::G2 G2;
     __shared__ zd2 xb[NH * TNB * 16], yb[NH * TNB * 16];  // X_p before and after its diagonal block
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = lane & 15, lk = lane >> 4;
@@ -135,14 +144,14 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t
         if (p >= np || p < first) continue;  // uniform
         const G2 *di = inv + (int64_t)p * TNB * TNB + (16 * wave + lr) * TNB;
         V2 a[4];
-        load4(a, di, 0, lk, TNB - 1);
+        load4<T>(a, di, 0, lk, TNB - 1);
 #pragma unroll
         for (int h = 0; h < NH; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) xb[slot(h, e)] = zd2{(double)x[p][h][e].x, (double)x[p][h][e].y};
         __syncthreads();
         Acc c;
-        mul64(c, a, di, lk, lane, TNB - 1, xb);
+        mul64<T>(c, a, di, lk, lane, TNB - 1, xb);
 #pragma unroll
         for (int h = 0; h < NH; ++h)
 #pragma unroll
@@ -164,10 +173,10 @@ __device__ __forceinline__ void solve_strip(int wo, int n, const G2 *Tm, int64_t
             if (q < 0 || q > 3) continue;
             if (q >= np || q < first) continue;  // uniform
             const G2 *row = row_of(q);
-            load4(a, row, 0, lk, kmax);
+            load4<T>(a, row, 0, lk, kmax);
             if (!have) __syncthreads();  // yb is complete
             have = true;
-            mul64(c, a, row, lk, lane, kmax, yb);
+            mul64<T>(c, a, row, lk, lane, kmax, yb);
 #pragma unroll
             for (int h = 0; h < NH; ++h)
 #pragma unroll
@@ -185,11 +194,11 @@ template <typename T, bool UPPER>
 __global__ __launch_bounds__(256, 2) void k_block_solve(int wo, int n, const T *T_, int64_t ldt, int64_t sT,
                                                         const T *inv_, int64_t sI, T *X_, int64_t ldx,
                                                         int64_t sX, int tri) {
-    typedef dglobal<typename Tv<T>::v2u> G2;
+    typedef typename Tv<T>::G2 G2;
     const int64_t nt = (int64_t)gridDim.x * gridDim.y, l = blockIdx.x + (int64_t)gridDim.x * blockIdx.y;
     const int64_t n8 = nt / 8, t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;  // one matrix's strips on one XCD
     const int64_t b = t / gridDim.x;
-    solve_strip<T, UPPER, G2>(wo, n, (const G2 *)T_ + b * sT, ldt, (const G2 *)inv_ + b * sI, (G2 *)X_ + b * sX, ldx,
+    solve_strip<T, UPPER>(wo, n, (const G2 *)T_ + b * sT, ldt, (const G2 *)inv_ + b * sI, (G2 *)X_ + b * sX, ldx,
                               tri, (int)(t % gridDim.x) * 16 * NH);
 }
 
@@ -198,7 +207,7 @@ __global__ __launch_bounds__(256, 2) void k_block_solve(int wo, int n, const T *
 template <typename T, bool UPPER>
 __global__ __launch_bounds__(256, 2) void k_block_solve_group(const GemmItem *__restrict__ items, int n_items,
                                                               int64_t n_tiles) {
-    typedef dglobal<typename Tv<T>::v2u> G2;
+    typedef typename Tv<T>::G2 G2;
     const int64_t l = blockIdx.x, n8 = n_tiles / 8;
     const int64_t t = l < 8 * n8 ? (l % 8) * n8 + l / 8 : l;
     int a = 0, b = n_items - 1;
@@ -209,7 +218,7 @@ __global__ __launch_bounds__(256, 2) void k_block_solve_group(const GemmItem *__
     }
     const GemmItem g = items[a];
     const int64_t r = t - g.t0, bz = r / g.tx;
-    solve_strip<T, UPPER, G2>(g.M, g.N, (const G2 *)g.A + bz * g.sA, g.lda, (const G2 *)g.B + bz * g.sB,
+    solve_strip<T, UPPER>(g.M, g.N, (const G2 *)g.A + bz * g.sA, g.lda, (const G2 *)g.B + bz * g.sB,
                               (G2 *)g.C + bz * g.sC, g.ldc, g.K, (int)(r - bz * g.tx) * 16 * NH);
 }
 
