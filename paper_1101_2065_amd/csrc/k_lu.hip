@@ -272,7 +272,9 @@ __global__ __launch_bounds__(512) void k_getf2(int n, int kb, int w, Cx<T> *A, i
 //
 // Measured, 256 panels of 64 columns side by side (rows moved and reloaded by
 // every chunk, five barriers and a shuffle tree per column before): 64 rows 354
-// -> 142 us, 431 rows 375 -> 250, 2000 rows about 1110 -> 830.  Of the 480k
+// -> 142 us, 431 rows 375 -> 250, 2000 rows about 1110 -> 830; the panels of a
+// solve of 64 frequencies and the lone one, 3072 rows 137 -> 85 ms, 4096 rows 262
+// -> 164 (FP32: 83 -> 63 and 176 -> 143).  Of the 480k
 // cycles at 431 rows the columns take 174k (2700 each), the update 94k, the
 // chunk loads and stores 57k and 54k, the two inverses 41k.
 //
