@@ -494,7 +494,8 @@ bool a_mesh_ok(int n_omega) { return !a_transform_fft() || (n_omega >= 128 && n_
 gw_status a_route_ws(gw_ctx *c, const std::string &pre, int n, int nhb, int n_omega, ARouteWs *w) {
     const size_t nn = (size_t)n * n;
     w->ldd = n + (n & 1);
-    w->xs = (int64_t)nn + (a_transform_fft() ? 0 : (nn & 1));
+    w->fft = a_transform_fft();
+    w->xs = (int64_t)nn + (w->fft ? 0 : (nn & 1));
     const size_t dd = (size_t)n * w->ldd;
     // dense bins staged at most 2 GiB at a time (at least one bin)
     w->dchunk = (int)std::max<size_t>(1, std::min<size_t>((size_t)std::max(1, nhb - 1), ((size_t)2 << 30) / (8 * dd)));
@@ -547,7 +548,7 @@ gw_status a_from_bins_enqueue(gw_ctx *ctx, hipStream_t st, int n, int n_omega, i
 
 gw_status a_transform_enqueue(gw_ctx *ctx, hipStream_t st, int n, int n_omega, int nhb, const ARouteWs &w,
                               const zdbl *Kt, const zdbl *tw, int j0, double domega, double eps, void *A_out) {
-    if (a_transform_fft()) GW_HIP(ctx, gwk::launch_fftconv_A(st, n, n_omega, nhb, w.B, Kt, tw, (zdbl *)A_out));
+    if (w.fft) GW_HIP(ctx, gwk::launch_fftconv_A(st, n, n_omega, nhb, w.B, Kt, tw, (zdbl *)A_out));
     else GW_HIP(ctx, gwk::launch_cauchy_A(st, n, n_omega, nhb, j0, domega, eps, w.B, w.xs, w.T, (zdbl *)A_out));
     return GW_OK;
 }

@@ -72,12 +72,14 @@ gw_status build_enqueue(gw_ctx *c, const BuildPlan &p, hipStream_t st, void *chi
 // bins) and the Cauchy-transform matrix T of the solved half of the mesh.
 // Rows are padded to an even number of values (ldd per row of D, xs per bin of
 // B), which the products' 16-byte copies need; V: room for v with rows of ldd
-// values (it holds bin 0 of B until that is formed), null for an even n.
+// values (it holds bin 0 of B until that is formed), null for an even n.  fft: the
+// transform that the rows were laid out for.
 struct ARouteWs {
     double *D = nullptr, *B = nullptr, *V = nullptr;
     zdbl *T = nullptr;
     int dchunk = 1;
     int64_t ldd = 0, xs = 0;
+    bool fft = false;
 };
 // GW_A_TRANSFORM=fft: the A route's transform by FFT convolution (meshes of
 // 128 to 1024 points) instead of the matrix product (any mesh).
